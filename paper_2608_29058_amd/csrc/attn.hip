@@ -34,6 +34,7 @@
 #include <cstring>
 #include <map>
 #include <tuple>
+#include <type_traits>
 #include <vector>
 
 #include "common.h"
@@ -91,14 +92,23 @@ __device__ __forceinline__ void lds_fence_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// Vertical-slash bitmap words of one wave's rows and one 64-key tile.  A wave's 32 rows start
+// at a multiple of 32, as the tile's keys do, so the diagonals i - j of its rows lie in the same
+// three words for every lane: d[k] = word wt - 2 + k, wt = (first row - first key) / 32.
+struct MaskWords {
+  uint32_t d[3];
+  uint32_t v[2];  // the tile's column bits
+};
+typedef uint32_t u32x3_a4 __attribute__((ext_vector_type(3), aligned(4)));
+typedef uint32_t u32x2_a4 __attribute__((ext_vector_type(2), aligned(4)));
+
 // Per-tile description produced ahead of its use (the next tile is issued while the
 // current one is computed).
 struct TileRef {
   int key0;  // first key of a contiguous tile, or -(1 + gather offset)
   int tag;   // bit 0: rows of waves 0-1 use it, bit 1: rows of waves 2-3 (block-sparse)
-  Win3 wd;   // vertical-slash: diagonal-bitmap words of this lane's row (prefetched)
-  Win3 wv;   // vertical-slash: column-bitmap words of the tile (prefetched)
   int hm;    // 32-key halves of the tile that are copied and may be kept (bit 0: keys 0-31)
+  MaskWords mw;  // vertical-slash: the tile's bitmap words (prefetched)
 };
 
 // bit 2m of the result: either of bits 2m, 2m + 1 of w (64-key tile m of a word of 32-key halves)
@@ -162,6 +172,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
   // ---- tile enumeration state ----------------------------------------------------------
   int ntiles = 0;
   int st0 = 0, st1 = 0;  // pattern cursors
+  [[maybe_unused]] int st_raw = 0;  // vertical-slash: the cursor's bitmap word (both halves of each tile)
   // block-sparse: key blocks selected by query block bq (sBA) and bq + 1 (sBB) as bitmaps;
   // words for key blocks 0 .. bq + 1, where bq + 1 reaches kMaxTiles for the last 64-row item
   // of a sequence of the maximum length
@@ -227,10 +238,10 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
     }
     n_gather = min(total, kMaxGather);
     __syncthreads();
-    ntiles = n_contig + (n_gather + 63) / 64;
     // contiguous tiles are taken from the diagonal down (descending keys)
     st0 = nwt - 1;                                                            // bitmap word of the next contiguous tile
-    st1 = __builtin_amdgcn_readfirstlane((int)tile_bits(sTB[st0]));           // remaining tiles (even bits)
+    st_raw = __builtin_amdgcn_readfirstlane((int)sTB[st0]);
+    st1 = (int)tile_bits((uint32_t)st_raw);                                   // remaining tiles (even bits)
   } else if constexpr (PAT == P_DENSE) {
     ntiles = last_tile + 1;
   } else if constexpr (PAT == P_ASHAPE) {
@@ -273,14 +284,20 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
     st1 = __builtin_amdgcn_readfirstlane((int)(sBA[st0] | sBB[st0]));  // remaining blocks of that word
   }
 
-  // next tile in order (t increases by one per call)
+  // next tile in order (t increases by one per call; g_next counts the gathered tiles, a phase
+  // of their own after the contiguous ones)
   int t_next = 0;
-  auto next_tile = [&]() -> TileRef {
-    const int t = t_next++;
+  [[maybe_unused]] int g_next = 0;
+  // zero in a vector register the compiler cannot see through: the mask words are the same for
+  // every lane, but a scalar load in flight would turn every LDS wait into a full drain
+  [[maybe_unused]] int vzero = 0;
+  if constexpr (PAT == P_VS) asm volatile("" : "+v"(vzero));
+  auto next_tile = [&](auto gathered) -> TileRef {
     if constexpr (PAT == P_DENSE) {
-      return TileRef{t * 64, 3, {0u, 0u, 0u}, {0u, 0u, 0u}, 3};
+      return TileRef{(t_next++) * 64, 3, 3, {}};
     } else if constexpr (PAT == P_ASHAPE) {
-      return TileRef{(t < st0 ? t : st1 + (t - st0)) * 64, 3, {0u, 0u, 0u}, {0u, 0u, 0u}, 3};
+      const int t = t_next++;
+      return TileRef{(t < st0 ? t : st1 + (t - st0)) * 64, 3, 3, {}};
     } else if constexpr (PAT == P_BS) {
       // the words are the same for every lane: kept in scalar registers
       while (st1 == 0) {
@@ -291,23 +308,35 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
       st1 &= ~(1u << bit);
       const int wa = __builtin_amdgcn_readfirstlane((int)sBA[st0]), wb = __builtin_amdgcn_readfirstlane((int)sBB[st0]);
       const int tag = ((wa >> bit) & 1) | (((wb >> bit) & 1) << 1);
-      return TileRef{(st0 * 32 + bit) * 64, tag, {0u, 0u, 0u}, {0u, 0u, 0u}, 3};
+      return TileRef{(st0 * 32 + bit) * 64, tag, 3, {}};
+    } else if constexpr (decltype(gathered)::value) {
+      return TileRef{-(1 + 64 * g_next++), 3, 3, {}};
     } else {
-      if (t < n_contig) {
-        // the bitmap words are the same for every lane: kept in scalar registers
-        while (st1 == 0) st1 = __builtin_amdgcn_readfirstlane((int)tile_bits(sTB[--st0]));
-        const int bit = 31 - __builtin_clz((uint32_t)st1);
-        st1 &= ~(1u << bit);
-        const int key0 = (st0 * 16 + (bit >> 1)) * 64;
-        const int hm = (__builtin_amdgcn_readfirstlane((int)sTB[st0]) >> bit) & 3;
-        TileRef tr{key0, 3, {0u, 0u, 0u}, {0u, 0u, 0u}, hm};
-        // bitmap words of the element mask, fetched with the tile so that their latency
-        // hides behind the previous tile's compute
-        tr.wd = load_win(dbits, a.nwords, my_row - key0 - 63);
-        tr.wv = load_win(vbits, a.nwords, key0);
-        return tr;
+      // the bitmap word is the same for every lane: kept in scalar registers
+      while (st1 == 0) {
+        st_raw = __builtin_amdgcn_readfirstlane((int)sTB[--st0]);
+        st1 = (int)tile_bits((uint32_t)st_raw);
       }
-      return TileRef{-(1 + (t - n_contig) * 64), 3, {0u, 0u, 0u}, {0u, 0u, 0u}, 3};
+      const int bit = 31 - __builtin_clz((uint32_t)st1);
+      st1 &= ~(1u << bit);
+      const int key0 = (st0 * 16 + (bit >> 1)) * 64;
+      TileRef tr{key0, 3, (st_raw >> bit) & 3, {}};
+      // bitmap words of the element mask, fetched with the tile so that their latency hides
+      // behind the previous tile's compute; words before the bitmap (keys after a row) are 0
+      if (wave_active) {
+        const int wt = (wbase >> 5) - (key0 >> 5), wv = key0 >> 5;
+        if (wt >= 2) {  // every key of the tile lies before the wave's rows, and so inside both bitmaps
+          const u32x3_a4 d = *(const u32x3_a4 *)(dbits + (wt - 2) + vzero);
+          const u32x2_a4 v = *(const u32x2_a4 *)(vbits + wv + vzero);
+          tr.mw = MaskWords{{d[0], d[1], d[2]}, {v[0], v[1]}};
+        } else {
+#pragma unroll
+          for (int k = 0; k < 3; ++k) tr.mw.d[k] = wt - 2 + k >= 0 ? dbits[wt - 2 + k + vzero] : 0u;
+#pragma unroll
+          for (int k = 0; k < 2; ++k) tr.mw.v[k] = wv + k < a.nwords ? vbits[wv + k + vzero] : 0u;
+        }
+      }
+      return tr;
     }
   };
 
@@ -323,12 +352,10 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
   }
 
   // ---- tile loads: global -> LDS (direct for bf16, through registers for fp32) ----------
-  auto key_of_row = [&](int key0, int row) -> int {
-    if constexpr (PAT == P_VS) {
-      if (key0 < 0) {
-        const int g = -key0 - 1 + row;
-        return sG[g < n_gather ? g : -key0 - 1];
-      }
+  auto key_of_row = [&](auto gathered, int key0, int row) -> int {
+    if constexpr (decltype(gathered)::value) {
+      const int g = -key0 - 1 + row;
+      return sG[g < n_gather ? g : -key0 - 1];
     }
     return min(key0 + row, a.n - 1);
   };
@@ -354,7 +381,8 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
   [[maybe_unused]] const uint32_t voVT =
       (uint32_t)(8 * wave + lane / 8) * bVT + 16u * (uint32_t)((lane % 8) ^ ((4 * (wave & 1) + (lane >> 4)) & 7));
   // one K or V tile (64 key rows) into dst
-  auto issue = [&](bf16 *dst, int key0, bool isV, int hm) {
+  auto issue = [&](auto gathered, bf16 *dst, int key0, bool isV, int hm) {
+    constexpr bool kG = decltype(gathered)::value;
     if constexpr (VT) {
       if (isV) {
         constexpr int LPV = D / 8 / NW;  // 8-row groups per wave
@@ -375,7 +403,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
       bf16 *dw = dst + wave * RPI * D;
       // load i copies tile rows [i NW RPI, (i + 1) NW RPI), inside 32-row half (i NW RPI) / 32
       // loads [h LPT / 2, (h + 1) LPT / 2) fill 32-key half h (one test of hm per half)
-      if (key0 >= 0 && key0 + 64 <= a.n) {  // contiguous rows: offsets are scalar
+      if (!kG && key0 + 64 <= a.n) {  // contiguous rows: offsets are scalar
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           if (!((hm >> h) & 1)) continue;
@@ -387,7 +415,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
       } else {  // gathered rows, or the last tile (rows clamped to the sequence)
         uint32_t jr[4];  // (LPT <= 4) every row index first: one LDS round trip for a gathered tile
 #pragma unroll
-        for (int i = 0; i < LPT; ++i) jr[i] = (uint32_t)key_of_row(key0, lrow0 + i * NW * RPI);
+        for (int i = 0; i < LPT; ++i) jr[i] = (uint32_t)key_of_row(gathered, key0, lrow0 + i * NW * RPI);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
           if (!((hm >> h) & 1)) continue;
@@ -404,7 +432,7 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
         const int row_base = (i * NW + wave) * RPI;
         const int row = row_base + lane / CPR;
         const int cc = (lane % CPR) ^ swz<D>(row);
-        const int j = key_of_row(key0, row);
+        const int j = key_of_row(gathered, key0, row);
         *(u32x4 *)(dst + row_base * D + 8 * lane) = load8<InT>(src + (long long)j * st + 8 * cc);
       }
     }
@@ -443,11 +471,12 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
   // ---- per-tile plan of this wave: participation, mask need, active 32-key halves ---------
   struct Plan {
     bool on, need_mask, do0, do1;
-    uint64_t Mvs;  // vertical-slash contiguous tile: this lane's kept keys (after half shift)
-    int g0, g_cnt; // vertical-slash gathered tile: first column slot, column count
+    uint32_t m0, m1;  // vertical-slash contiguous tile: this lane's kept keys of each half (after half shift)
+    int g0, g_cnt;    // vertical-slash gathered tile: first column slot, column count
   };
-  auto plan_of = [&](const TileRef &tr, bool valid) -> Plan {
-    Plan p{false, true, true, true, 0ull, 0, 0};
+  [[maybe_unused]] const uint32_t dsh = 31u - (uint32_t)(my_row & 31);
+  auto plan_of = [&](auto gathered, const TileRef &tr, bool valid) -> Plan {
+    Plan p{false, true, true, true, 0u, 0u, 0, 0};
     if (!valid) return p;
     const int key0 = tr.key0;
     if constexpr (kOverlap) {
@@ -460,21 +489,32 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
     }
     if (!wave_active || !(tr.tag & my_rows_tag)) return p;
     if constexpr (PAT == P_VS) {
-      if (key0 < 0) {
+      if constexpr (decltype(gathered)::value) {
         p.g0 = -key0 - 1;
         p.g_cnt = min(64, n_gather - p.g0);
         p.on = sG[p.g0] <= w_hi;
         p.do1 = p.g_cnt > 32;
+        // columns are ascending: the last one before every row of the wave, every slot used
+        p.need_mask = p.g_cnt < 64 || sG[p.g0 + p.g_cnt - 1] > w_lo;
       } else if (key0 <= w_hi) {
         // the lane's kept keys are known before any product: a 32-key half no row of the
-        // wave keeps skips both of its products
-        const int i = my_row;
-        const uint64_t md = __builtin_bitreverse64(win_bits(tr.wd, i - key0 - 63));
-        const uint64_t mv = win_bits(tr.wv, key0);
-        const uint64_t halves = (tr.hm & 1 ? 0xffffffffull : 0ull) | (tr.hm & 2 ? 0xffffffff00000000ull : 0ull);
-        p.Mvs = ((md | mv) & prefix_mask(i - key0 + 1) & halves) >> (4 * hh);
-        p.do0 = __ballot(((uint32_t)p.Mvs & 0x0f0f0f0fu) != 0u) != 0ull;
-        p.do1 = __ballot(((uint32_t)(p.Mvs >> 32) & 0x0f0f0f0fu) != 0u) != 0ull;
+        // wave keeps skips both of its products.  Diagonals i - j: the reversed words, shifted
+        // so that bit 0 of the first is diagonal i - key0; keys after the row read zero words.
+        const uint32_t r0 = __builtin_bitreverse32(tr.mw.d[2]), r1 = __builtin_bitreverse32(tr.mw.d[1]),
+                       r2 = __builtin_bitreverse32(tr.mw.d[0]);
+        uint32_t lo = __builtin_amdgcn_alignbit(r1, r0, dsh) | tr.mw.v[0];
+        uint32_t hi = __builtin_amdgcn_alignbit(r2, r1, dsh) | tr.mw.v[1];
+        if (key0 + 64 > wbase) {  // columns after the row
+          const uint64_t pm = prefix_mask(my_row - key0 + 1);
+          lo &= (uint32_t)pm;
+          hi &= (uint32_t)(pm >> 32);
+        }
+        if (!(tr.hm & 1)) lo = 0u;  // halves that were not copied (their columns are gathered)
+        if (!(tr.hm & 2)) hi = 0u;
+        p.m0 = lo >> (4 * hh);
+        p.m1 = hi >> (4 * hh);
+        p.do0 = __ballot((p.m0 & 0x0f0f0f0fu) != 0u) != 0ull;
+        p.do1 = __ballot((p.m1 & 0x0f0f0f0fu) != 0u) != 0ull;
         p.on = p.do0 || p.do1;
       }
     } else {  // block-sparse
@@ -518,9 +558,9 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
 #pragma unroll
     for (int mb = 0; mb < 2; ++mb) {
       const bool dm = mb ? p.do1 : p.do0;
+      if (!dm) continue;  // the mask drops every element of the half, whatever it holds
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[mb][r] = 0.f;
-      if (!dm) continue;
       auto kread = [&](int ks) -> u32x4 {
         return *(const u32x4 *)&sKt[(32 * mb + l32) * D + (((2 * ks + hh) ^ kswz) << 3)];
       };
@@ -546,11 +586,11 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
 
   // ---- masks: this lane's keys are bits 0-3 of every byte of M (after the half shift); a
   // kept key keeps its logit, a dropped one (or a skipped half) becomes -inf ---------------
-  auto apply_mask = [&](f32x16 (&s)[2], const TileRef &tr, const Plan &p) -> bool {
+  auto apply_mask = [&](auto gathered, f32x16 (&s)[2], const TileRef &tr, const Plan &p) -> bool {
     const int key0 = tr.key0, i = my_row;
     uint64_t M;
     if constexpr (PAT == P_VS) {
-      if (key0 < 0) {
+      if constexpr (decltype(gathered)::value) {
         int lo = 0, hi = p.g_cnt;
         while (lo < hi) {
           const int mid = (lo + hi) >> 1;
@@ -559,10 +599,8 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
         }
         M = prefix_mask(lo) >> (4 * hh);
       } else {
-        M = p.Mvs;
+        M = (uint64_t)p.m0 | ((uint64_t)p.m1 << 32);
       }
-      if (!p.do0) M &= ~0xffffffffull;
-      if (!p.do1) M &= 0xffffffffull;
     } else if constexpr (PAT == P_ASHAPE) {
       const uint64_t keep = prefix_mask(U.sink - key0) | ~prefix_mask(i - U.window + 1 - key0);
       M = (keep & prefix_mask(i - key0 + 1)) >> (4 * hh);
@@ -677,20 +715,21 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
   // On entry sc holds S^T of tile t; K of tile t+1 (in kn) and V of tile t (in vc) are resident
   // after the barrier.  The step copies K of tile t+2 into kc (released by tile t's products)
   // and V of tile t+1 into vn (released by tile t-1's P V).
-  TileRef Tc{0, 0, {0u, 0u, 0u}, {0u, 0u, 0u}, 3}, Tn = Tc;
-  Plan Pc = plan_of(Tc, false), Pn = Pc;
-  auto step = [&](int t, f32x16 (&sc)[2], f32x16 (&sn)[2], bf16 *kc, bf16 *kn, bf16 *vc, bf16 *vn) {
+  TileRef Tc{0, 0, 3, {}}, Tn = Tc;
+  Plan Pc{}, Pn{};
+  auto step = [&](auto gathered, int t, const int nt, f32x16 (&sc)[2], f32x16 (&sn)[2], bf16 *kc, bf16 *kn, bf16 *vc,
+                  bf16 *vn) {
     // the next tile is taken after the barrier: the barrier waits for every load in flight,
     // and the vertical-slash mask words that next_tile fetches are only needed a step later
     lds_fence_barrier();
-    TileRef T2{0, 0, {0u, 0u, 0u}, {0u, 0u, 0u}, 3};
-    if (t + 2 < ntiles) T2 = next_tile();
-    if (t + 2 < ntiles) issue(kc, T2.key0, false, T2.hm);
-    if (t + 1 < ntiles) issue(vn, Tn.key0, true, Tn.hm);
-    Pn = plan_of(Tn, t + 1 < ntiles);
+    TileRef T2{0, 0, 3, {}};
+    if (t + 2 < nt) T2 = next_tile(gathered);
+    if (t + 2 < nt) issue(gathered, kc, T2.key0, false, T2.hm);
+    if (t + 1 < nt) issue(gathered, vn, Tn.key0, true, Tn.hm);
+    Pn = plan_of(gathered, Tn, t + 1 < nt);
     bool has_key = true;
     if (kOverlap || Pc.on)
-      if (PAT == P_VS || Pc.need_mask) has_key = apply_mask(sc, Tc, Pc);
+      if (Pc.need_mask) has_key = apply_mask(gathered, sc, Tc, Pc);
     // tile t+1's products, then tile t's softmax: the two waves of a SIMD tend to alternate
     // between product bursts and softmax bursts, so that one's products overlap the other's
     // vector work (interleaving them within a wave was measured slower)
@@ -738,22 +777,38 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
 
   // ---- main loop ---------------------------------------------------------------------------
   f32x16 sA[2], sB[2];
-  if (ntiles > 0) {
-    Tc = next_tile();
-    issue(sK0, Tc.key0, false, Tc.hm);
-    issue(sV0, Tc.key0, true, Tc.hm);
-    if (ntiles > 1) {
-      Tn = next_tile();
-      issue(sK1, Tn.key0, false, Tn.hm);
+  if constexpr (PAT == P_VS) {  // skipped halves are masked without being computed
+#pragma unroll
+    for (int mb = 0; mb < 2; ++mb)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sA[mb][r] = sB[mb][r] = 0.f;
+  }
+  auto run_tiles = [&](auto gathered, const int nt) {
+    if (nt <= 0) return;
+    Tc = next_tile(gathered);
+    issue(gathered, sK0, Tc.key0, false, Tc.hm);
+    issue(gathered, sV0, Tc.key0, true, Tc.hm);
+    if (nt > 1) {
+      Tn = next_tile(gathered);
+      issue(gathered, sK1, Tn.key0, false, Tn.hm);
     }
     lds_fence_barrier();
-    Pc = plan_of(Tc, true);
+    Pc = plan_of(gathered, Tc, true);
     if (kOverlap || Pc.on) qk(sA, sK0, Pc);
-  }
-  for (int t = 0; t < ntiles; t += 2) {
-    step(t, sA, sB, sK0, sK1, sV0, sV1);
-    if (t + 1 >= ntiles) break;
-    step(t + 1, sB, sA, sK1, sK0, sV1, sV0);
+    for (int t = 0; t < nt; t += 2) {
+      step(gathered, t, nt, sA, sB, sK0, sK1, sV0, sV1);
+      if (t + 1 >= nt) break;
+      step(gathered, t + 1, nt, sB, sA, sK1, sK0, sV1, sV0);
+    }
+  };
+  if constexpr (PAT == P_VS) {
+    // contiguous tiles, then gathered ones, each with a loop of its own: neither carries the
+    // other's addressing or masks
+    run_tiles(std::false_type{}, n_contig);
+    if (n_contig > 0 && n_gather > 0) lds_fence_barrier();  // every wave is done with the tile buffers
+    run_tiles(std::true_type{}, (n_gather + 63) / 64);
+  } else {
+    run_tiles(std::false_type{}, ntiles);
   }
 
   // ---- epilogue --------------------------------------------------------------------------
