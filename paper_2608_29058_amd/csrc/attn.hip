@@ -126,9 +126,10 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
   constexpr int LPT = 64 / RPI / NW;     // loads per thread per K (or V) tile
   constexpr int TE = 64 * D;             // elements of one K or V tile
   static_assert(LPT % 2 == 0 && LPT <= 4 && LPT * NW * RPI == 64, "K/V copies: two halves of LPT / 2 loads");
-  // fragment reads in flight ahead of the products (K for QK^T, V for P V); vertical-slash
-  // keeps two (its tile bookkeeping leaves fewer registers; more spill)
-  constexpr int KPF = PAT == P_VS ? 2 : 4;
+  // fragment reads in flight ahead of the products (K for QK^T, V for P V).  Vertical-slash
+  // keeps two for V (three: the same time within 0.5%); four for K instead of two took the
+  // routed 128K layer from 23.1 to 22.5 ms (its launch 7.0 -> 6.4 ms).
+  constexpr int KPF = 4;
   constexpr int VPF = PAT == P_VS ? 2 : 3;
   // the products of the tile-skipping families sit under a branch, where the compiler puts
   // each K read right before its product unless the order is forced (scheduling groups)
