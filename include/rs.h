@@ -15,8 +15,7 @@
  *    until the work queued on `stream` has finished.  Host pointers are read before the
  *    call returns.
  *  - The library allocates no device memory: calls that need scratch space take a
- *    caller-provided workspace whose size a *_workspace_size() query returns (the one
- *    exception, rs_route_layer_device_noalloc, uses a fixed static device array instead).
+ *    caller-provided workspace whose size a *_workspace_size() query returns.
  *  - GPU calls are asynchronous on `stream` (a hipStream_t; NULL = the null stream).
  *    rs_route_layer is host-only, synchronous and pure.
  *  - Every call returns an rs_status; on failure nothing has been launched and
@@ -300,14 +299,10 @@ rs_status rs_route_layer_device(const rs_route_in *in, const rs_route_cfg *cfg,
 /* ---- device routing without a workspace ---------------------------------------------------
  * For callers that cannot allocate device memory (code under HIP graph capture, tight serving
  * loops, harnesses that forbid hipMalloc): rs_route_layer_device with the same arguments,
- * validation and results (bit for bit), except that the router's scratch lives in a fixed
- * library-owned device array of 96 KiB per GPU (one copy per device the library runs on,
- * held until the process ends) instead of a caller workspace.  The call allocates nothing.
- * Every call on one GPU shares that GPU's array, and the kernel writes every scratch element
- * before reading it, so consecutive calls need no clearing; calls that overlap on one GPU
- * (concurrent streams, several threads) race on the array and must be serialised by the
- * caller.  Limits: nunits <= 2048 and nunits * (ncand - 1) <= 4096, the largest sizes the
- * array holds; beyond them RS_ERR_UNSUPPORTED, with nothing launched. */
+ * validation and results (bit for bit), but no workspace argument: the router's scratch lives
+ * in LDS.  The call allocates nothing and shares nothing with other calls.
+ * Limits: nunits <= 2048 and nunits * (ncand - 1) <= 4096; beyond them RS_ERR_UNSUPPORTED, with
+ * nothing launched. */
 rs_status rs_route_layer_device_noalloc(const rs_route_in *in, const rs_route_cfg *cfg,
                                         const rs_route_dev_out *out, rs_stream stream);
 

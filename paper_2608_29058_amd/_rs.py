@@ -453,7 +453,7 @@ def rs_route_layer_device(rb, cov, nsub, t_probe_us, T_layer_us, tau, alpha, bet
 
 def rs_route_layer_device_noalloc(rb, cov, nsub, t_probe_us, T_layer_us, tau, alpha, beta, delta_q, e=None,
                                   stream=None):
-    """As rs_route_layer_device, with the library's fixed scratch instead of rb.ws."""
+    """As rs_route_layer_device, without a workspace."""
     rin = RsRouteIn(nunits=rb.U, ncand=rb.C, grid=C.cast(rb.grid, P), cov=cov.data_ptr(), nsub=nsub.data_ptr(),
                     e=e.data_ptr() if e is not None else None, s1=rb.s1.data_ptr(),
                     t_table=rb.t_table.data_ptr(), bucket_edge=rb.bucket_edge.data_ptr(), nbucket=rb.nbucket,
