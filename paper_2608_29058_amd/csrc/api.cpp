@@ -109,7 +109,7 @@ rs_status check_unit_table(const rs_unit_table *t, const rs_qkv *qkv, const rs_u
 }
 
 // defined in the .hip translation units
-size_t attn_ws_bytes(const rs_unit *units, int32_t nunits);
+size_t attn_ws_bytes(const rs_qkv *qkv, const rs_unit *units, int32_t nunits);
 rs_status attn_launch(const rs_qkv *qkv, float scale, const rs_unit *units, int32_t nunits, int fam,
                       const rs_candidate *cand, int cand_local, const rs_index_set *idx, void *o, int64_t so_h,
                       int64_t so_t, float *lse, void *ws, size_t ws_bytes, hipStream_t st);
@@ -156,7 +156,7 @@ rs_status route_dev_launch_noalloc(const rs_route_in *in, const rs_route_cfg *cf
                                    const int *fam, const int *brank, int dense_c, hipStream_t st);
 rs_status error_predict_launch(const rs_probe_out *p, const rs_candidate *grid, int32_t ncand,
                                const rs_error_model *m, float *e, hipStream_t st);
-size_t routed_attn_ws_bytes(const rs_unit *units, int32_t nunits);
+size_t routed_attn_ws_bytes(const rs_qkv *qkv, const rs_unit *units, int32_t nunits);
 rs_status routed_attn_launch(const rs_qkv *qkv, float scale, const rs_unit *units, int32_t nunits,
                              const rs_candidate *grid, int32_t ncand, const rs_index_set *idx, const int32_t *choice,
                              void *o, int64_t so_h, int64_t so_t, float *lse, void *ws, size_t ws_bytes,
@@ -186,9 +186,8 @@ const char *rs_last_error(void) { return g_err.c_str(); }
 const char *rs_version(void) { return "routesparse-mi355x 0.1 (gfx950)"; }
 
 size_t rs_attn_workspace_size(const rs_qkv *qkv, const rs_unit *units, int32_t nunits) {
-  (void)qkv;
   if (nunits <= 0 || !units) return 256;
-  return attn_ws_bytes(units, nunits);
+  return attn_ws_bytes(qkv, units, nunits);
 }
 
 rs_status rs_dense_attn_prefill(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, void *o, int64_t so_h,
@@ -450,9 +449,8 @@ rs_status rs_error_predict(const rs_probe_out *probe, const rs_candidate *grid, 
 }
 
 size_t rs_routed_attn_workspace_size(const rs_qkv *qkv, const rs_unit *units, int32_t nunits) {
-  (void)qkv;
   if (nunits <= 0 || !units) return 256;
-  return routed_attn_ws_bytes(units, nunits);
+  return routed_attn_ws_bytes(qkv, units, nunits);
 }
 
 rs_status rs_routed_attn_prefill(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, const rs_candidate *grid,

@@ -63,6 +63,7 @@ struct AttnArgs {
   int nv_max, ns_max, nwords, ncand_vs;
   const int *bs_sorted, *bs_count;
   int k_max, nb, ncand_bs;
+  AttnParts parts;  // partial results of split items (dense and vertical-slash)
 };
 
 constexpr int kMaxTiles = kMaxN / 64;  // key tiles of the longest supported sequence
@@ -114,7 +115,8 @@ struct TileRef {
 // bit 2m of the result: either of bits 2m, 2m + 1 of w (64-key tile m of a word of 32-key halves)
 __device__ __forceinline__ uint32_t tile_bits(uint32_t w) { return (w | (w >> 1)) & 0x55555555u; }
 
-// One work item: query tile `item & 0xffff` of unit `item >> 16` of the launch's unit list.
+// One work item: piece `item >> 12 & 15` of query tile `item & 0xfff` of unit `item >> 16` of the
+// launch's unit list.
 // VT: V is read from the transposed copy (tiles of D rows x 64 keys), else from V itself.
 template <int D, int PAT, typename InT, bool VT>
 __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
@@ -143,13 +145,30 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
   __shared__ __align__(16) bf16 sV0[TE];
   __shared__ __align__(16) bf16 sV1[TE];
 
-  const int tid = threadIdx.x;
+  // opaque: what the set-up and the epilogue derive from it is computed again for every item
+  // instead of being kept in registers across a persistent workgroup's item loop, where
+  // vertical-slash (19 spilled registers) ran 9.0 instead of 6.2 ms on a routed 128K layer.  (Reading
+  // the arguments again per item as well saves scalar spills but costs dense 2%.)
+  int tid = threadIdx.x;
+  if constexpr (PAT == P_VS || PAT == P_BS) asm volatile("" : "+v"(tid));
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
 
   const DevUnit U = a.units[item >> 16];
-  const int qt = item & 0xffff;
+  const int qt = item & 0xfff;
+  // pieces along the keys (dense and vertical-slash): this item takes the tiles of piece `piece`
+  constexpr bool kSplit = PAT == P_DENSE || PAT == P_VS;
+  [[maybe_unused]] const int piece = (item >> 12) & 15;
+  [[maybe_unused]] int npiece = kSplit ? U.nsplit : 1;
+  // pieces of this item's `nt` tiles: a short list takes fewer, and the workgroups beyond them have
+  // nothing to do (false)
+  [[maybe_unused]] auto take_piece = [&](int nt) -> bool {
+    const int pt = a.units[item >> 16].ptiles;
+    npiece = min(npiece, max(1, (nt + pt - 1) / pt));
+    if (piece == 0 && threadIdx.x == 0) a.parts.n[a.units[item >> 16].pbase + qt * a.units[item >> 16].nsplit] = npiece;
+    return piece < npiece;
+  };
   const int head = U.head, s0 = U.s0, s1 = U.s1;
   const int kvh = head / a.group;
   // A block-sparse unit with a mate runs 64-row items: waves 0-1 take its rows of query block
@@ -180,6 +199,8 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
   __shared__ uint32_t sBA[PAT == P_BS ? kMaxTiles / 32 + 1 : 1], sBB[PAT == P_BS ? kMaxTiles / 32 + 1 : 1];
   const uint32_t *vbits = nullptr, *dbits = nullptr;
   int n_contig = 0, n_gather = 0;
+  [[maybe_unused]] int g_first = 0, n_gtiles = 0;  // vertical-slash: gathered tiles of this item's piece
+  [[maybe_unused]] int t_first = 0;                // dense: first tile of this item's piece
   // vertical-slash: sTB, one bit per 32-key half of the key range the block's diagonals touch
   // (a 64-key tile is in the list when either of its halves is, and only those halves are
   // copied); sG, the gathered vertical columns.  Arrays of their own, not pointers, so that
@@ -208,11 +229,14 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
       for (int kh = lo; kh <= hi; ++kh) atomicOr(&sTB[kh >> 5], 1u << (kh & 31));
     }
     __syncthreads();
-    {
-      int cnt = 0;
-      for (int w = 0; w < nwt; ++w) cnt += __builtin_popcount(tile_bits(sTB[w]));
-      n_contig = cnt;
+    // tiles per bitmap word, a word per lane (every wave sums the same words, no barrier)
+    for (int w0 = 0; w0 < nwt; w0 += 64) {
+      int cnt = w0 + lane < nwt ? __builtin_popcount(tile_bits(sTB[w0 + lane])) : 0;
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) cnt += __shfl_xor(cnt, o);
+      n_contig += cnt;
     }
+    n_contig = __builtin_amdgcn_readfirstlane(n_contig);
     // vertical columns outside the diagonal tiles are gathered, ascending
     int total = 0;
     for (int x0 = 0; x0 < nvc; x0 += NT) {
@@ -241,10 +265,50 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
     __syncthreads();
     // contiguous tiles are taken from the diagonal down (descending keys)
     st0 = nwt - 1;                                                            // bitmap word of the next contiguous tile
+    int skip = 0;                                                             // tiles before this item's piece
+    if (npiece > 1) {
+      // the list (contiguous tiles, then gathered ones) in pieces of equal length
+      const int nt = n_contig + ((n_gather + 63) >> 6);
+      if (!take_piece(nt)) return;
+      const int lo = (int)((long long)nt * piece / npiece), hi = (int)((long long)nt * (piece + 1) / npiece);
+      skip = min(lo, n_contig);
+      g_first = max(lo - n_contig, 0);
+      n_gtiles = max(hi - n_contig, 0) - g_first;
+      n_contig = min(hi, n_contig) - skip;
+      // cursor to the first tile of the piece: 64 words at a time, tiles above each word by a scan
+      int wtop = nwt - 1;
+      while (n_contig > 0) {
+        const int w = wtop - lane;
+        const int cnt = w >= 0 ? __builtin_popcount(tile_bits(sTB[w])) : 0;
+        int incl = cnt;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+          const int y = __shfl_up(incl, o);
+          if (lane >= o) incl += y;
+        }
+        const int all = __builtin_amdgcn_readlane(incl, 63);
+        if (all > skip) {  // the lane whose word holds tile number `skip`
+          const uint64_t m = __ballot(incl > skip);
+          const int l = __builtin_ctzll(m);
+          st0 = wtop - l;
+          skip -= __builtin_amdgcn_readlane(incl - cnt, l);
+          break;
+        }
+        skip -= all;
+        wtop -= 64;
+      }
+    } else {
+      n_gtiles = (n_gather + 63) >> 6;
+    }
     st_raw = __builtin_amdgcn_readfirstlane((int)sTB[st0]);
     st1 = (int)tile_bits((uint32_t)st_raw);                                   // remaining tiles (even bits)
+    if (n_contig > 0)
+      for (; skip > 0; --skip) st1 &= ~(1u << (31 - __builtin_clz((uint32_t)st1)));
   } else if constexpr (PAT == P_DENSE) {
-    ntiles = last_tile + 1;
+    const int nt = last_tile + 1;
+    if (npiece > 1 && !take_piece(nt)) return;
+    t_first = nt * piece / npiece;
+    ntiles = nt * (piece + 1) / npiece - t_first;
   } else if constexpr (PAT == P_ASHAPE) {
     const int ns = min((U.sink + 63) >> 6, last_tile + 1);
     const int wlo = max(0, r_lo - U.window + 1) >> 6;
@@ -287,8 +351,8 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
 
   // next tile in order (t increases by one per call; g_next counts the gathered tiles, a phase
   // of their own after the contiguous ones)
-  int t_next = 0;
-  [[maybe_unused]] int g_next = 0;
+  int t_next = t_first;
+  [[maybe_unused]] int g_next = g_first;
   // zero in a vector register the compiler cannot see through: the mask words are the same for
   // every lane, but a scalar load in flight would turn every LDS wait into a full drain
   [[maybe_unused]] int vzero = 0;
@@ -806,8 +870,8 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
     // contiguous tiles, then gathered ones, each with a loop of its own: neither carries the
     // other's addressing or masks
     run_tiles(std::false_type{}, n_contig);
-    if (n_contig > 0 && n_gather > 0) lds_fence_barrier();  // every wave is done with the tile buffers
-    run_tiles(std::true_type{}, (n_gather + 63) / 64);
+    if (n_contig > 0 && n_gtiles > 0) lds_fence_barrier();  // every wave is done with the tile buffers
+    run_tiles(std::true_type{}, n_gtiles);
   } else {
     run_tiles(std::false_type{}, ntiles);
   }
@@ -816,6 +880,27 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
   if (!wave_active) return;
   const float l_tot = l_run + __shfl_xor(l_run, 32);
   const int i = my_row;
+  if constexpr (kSplit) {
+    if (__builtin_expect(npiece > 1, 0)) {
+      // this piece's unnormalised O, running max and sum; attn_merge_kernel finishes the rows
+      if (i < r_lo || i >= r_hi) return;
+      const int slot0 = a.units[item >> 16].pbase + qt * a.units[item >> 16].nsplit;
+      const long long at = (long long)(slot0 + piece) * BM + (i - base);
+      float *po = a.parts.o + at * D;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int ii = 0; ii < 4; ++ii)
+          *(f32x4 *)(po + 32 * db + 8 * ii + 4 * hh) =
+              f32x4{oacc[db][4 * ii], oacc[db][4 * ii + 1], oacc[db][4 * ii + 2], oacc[db][4 * ii + 3]};
+      if (hh == 0) {
+        float *pm = a.parts.ml + at * 2;
+        pm[0] = m_run;
+        pm[1] = l_tot;
+      }
+      return;
+    }
+  }
   if (i < r_lo || i >= r_hi) return;
   const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
   bf16 *op = a.o + (long long)whead * a.so_h + (long long)i * a.so_t;
@@ -863,6 +948,83 @@ __global__ void __launch_bounds__(256, 2) attn_fwd_queue_kernel(const AttnArgs a
     if (it < 0) break;
     attn_item<D, PAT, InT, VT>(a, it);
   }
+}
+
+// ---- merge of split items ------------------------------------------------------------------
+// grid (slots, 8), 256 threads: 16 rows of an item per workgroup, 16 threads per row.  Piece p of
+// a row holds O_p relative to its own running max m_p: with M the largest and w_p = exp(m_p - M),
+// O = sum w_p O_p / sum w_p l_p, in piece order (a fixed order: the result is deterministic).  A
+// piece that kept no key of the row has l_p = 0 and m_p = -inf.  Bound by reading the pieces.
+template <int D>
+__global__ void __launch_bounds__(256) attn_merge_kernel(const DevUnit *units, const AttnParts parts, bf16 *o,
+                                                         long long so_h, long long so_t, float *lse, int n, float c,
+                                                         float scale) {
+  constexpr int EPT = D / 16, BM = 128;  // elements per thread, rows of an item
+  const int slot0 = blockIdx.x, item = parts.items[slot0];
+  if (item < 0) return;
+  const int np = parts.n[slot0];
+  if (np <= 1) return;  // the item's one workgroup wrote the rows itself
+  const DevUnit U = units[item >> 16];
+  const int base = (U.s0 / BM + (item & 0xfff)) * BM;
+  const int r = blockIdx.y * 16 + (threadIdx.x >> 4), i = base + r, x = threadIdx.x & 15;
+  if (i < U.s0 || i >= U.s1) return;
+  const float *ml = parts.ml + ((long long)slot0 * BM + r) * 2;
+  float M = -INFINITY;
+  for (int p = 0; p < np; ++p) M = fmaxf(M, ml[(long long)p * BM * 2]);
+  float acc[EPT], L = 0.f;
+#pragma unroll
+  for (int e = 0; e < EPT; ++e) acc[e] = 0.f;
+  const float *po = parts.o + ((long long)slot0 * BM + r) * D + EPT * x;
+  for (int p = 0; p < np; ++p) {
+    const float l = ml[(long long)p * BM * 2 + 1];
+    const float w = l > 0.f ? __builtin_amdgcn_exp2f((ml[(long long)p * BM * 2] - M) * c) : 0.f;
+    L += w * l;
+#pragma unroll
+    for (int e = 0; e < EPT; e += 4) {
+      const f32x4 v = *(const f32x4 *)(po + (long long)p * BM * D + e);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) acc[e + k] += w * v[k];
+    }
+  }
+  const float inv = L > 0.f ? 1.f / L : 0.f;
+  bf16 *op = o + (long long)U.head * so_h + (long long)i * so_t + EPT * x;
+#pragma unroll
+  for (int e = 0; e < EPT; e += 4)
+    *(u32x2 *)(op + e) = u32x2{pack_bf16x2(acc[e] * inv, acc[e + 1] * inv), pack_bf16x2(acc[e + 2] * inv, acc[e + 3] * inv)};
+  if (lse && x == 0) lse[(long long)U.head * n + i] = L > 0.f ? M * scale + logf(L) : -INFINITY;
+}
+
+size_t attn_parts_bytes(int d, size_t slots) {
+  if (slots == 0) return 0;
+  Arena ar(nullptr, 0);
+  ar.take<float>(slots * 128 * d);
+  ar.take<float>(slots * 128 * 2);
+  ar.take<int>(slots);
+  ar.take<int>(slots);
+  return ar.off + 256;
+}
+
+AttnParts attn_parts_at(void *p, int d, size_t slots) {
+  Arena ar(p, ~size_t(0));
+  AttnParts a;
+  a.o = ar.take<float>(slots * 128 * d);
+  a.ml = ar.take<float>(slots * 128 * 2);
+  a.n = ar.take<int>(slots);
+  a.items = ar.take<int>(slots);
+  return a;
+}
+
+rs_status attn_merge_launch(const rs_qkv *qkv, float scale, const DevUnit *d_units, const AttnParts &parts,
+                            int slots, void *o, int64_t so_h, int64_t so_t, float *lse, hipStream_t st) {
+  const dim3 grid(slots, 8);
+  if (qkv->d == 128)
+    hipLaunchKernelGGL(attn_merge_kernel<128>, grid, dim3(256), 0, st, d_units, parts, (bf16 *)o, (long long)so_h,
+                       (long long)so_t, lse, qkv->n, scale * kLog2e, scale);
+  else
+    hipLaunchKernelGGL(attn_merge_kernel<64>, grid, dim3(256), 0, st, d_units, parts, (bf16 *)o, (long long)so_h,
+                       (long long)so_t, lse, qkv->n, scale * kLog2e, scale);
+  RS_HIP(hipGetLastError());
+  return RS_OK;
 }
 
 // ---- V^T: [hkv][d][npad] bf16, keys permuted within groups of 16 ---------------------------
@@ -933,14 +1095,24 @@ static int family_bm(int) { return 128; }
 
 static int tiles_of(const rs_unit &u, int bm) { return (u.s1 - 1) / bm - u.s0 / bm + 1; }
 
+// Bytes of a launch's work list, without partial results: [DevUnit x nunits][items]
 // (a unit with a mate has at most twice its 128-row tiles in 64-row blocks, and its mate none)
-size_t attn_ws_bytes(const rs_unit *units, int32_t nunits) {
-  size_t items = 0;
-  for (int i = 0; i < nunits; ++i) items += (size_t)tiles_of(units[i], 128);
+static size_t attn_list_bytes(int32_t nunits, size_t items) {
   Arena ar(nullptr, 0);
   ar.take<DevUnit>((size_t)nunits);
   ar.take<int>(items);
-  return ar.off + 256;
+  return ar.off + 256;  // (rounded down to 256 bytes: at or past the list's end)
+}
+
+size_t attn_ws_bytes(const rs_qkv *qkv, const rs_unit *units, int32_t nunits) {
+  size_t items = 0, slots = 0;
+  for (int i = 0; i < nunits; ++i) {
+    const rs_unit &u = units[i];
+    const int s = qkv && u.s0 >= 0 && u.s1 > u.s0 && qkv->hq > 0 ? attn_split_slots(qkv->hq, qkv->d, u.s0, u.s1) : 0;
+    items += std::max<size_t>((size_t)tiles_of(u, 128), (size_t)s);
+    slots += (size_t)s;
+  }
+  return attn_list_bytes(nunits, items) + attn_parts_bytes(qkv ? qkv->d : 0, slots);
 }
 
 // Block-sparse mates: a unit of an even head takes along the unit of the next head with the
@@ -965,16 +1137,18 @@ static void pair_units(const rs_unit *units, int nunits, int group, std::vector<
 // dispatch places workgroup b on XCD b % 8, so the query heads sharing one K/V stream
 // share one XCD's L2), longest query tiles first within a bucket.  Items of a unit with a
 // mate are 64-row query blocks, others bm-row query tiles (bm = 128); units taken along by a
-// mate have none.
+// mate have none.  Pieces of a split item follow one another.
 static void build_order(const rs_unit *units, int nunits, int group, int bm, const std::vector<int> &mate,
-                        std::vector<int> &order) {
+                        const std::vector<SplitRule> &split, std::vector<int> &order) {
   std::vector<std::vector<std::pair<int, int>>> buckets(8);  // (-first row / 64, item)
   for (int u = 0; u < nunits; ++u) {
     if (mate[u] == -2) continue;
     const int im = mate[u] >= 0 ? 64 : bm;
     const int t0 = units[u].s0 / im, nt = tiles_of(units[u], im);
     const int b = (units[u].head / group) & 7;
-    for (int t = 0; t < nt; ++t) buckets[b].push_back({-((t0 + t) * (im / 64)), (u << 16) | t});
+    for (int t = 0; t < nt; ++t)
+      for (int p = 0; p < split[u].nsplit; ++p)
+        buckets[b].push_back({-((t0 + t) * (im / 64)), (u << 16) | (p << 12) | t});
   }
   size_t mx = 0;
   for (auto &b : buckets) {
@@ -1035,7 +1209,7 @@ static hipError_t launch_d(int fam, int dtype, const AttnArgs &a, int nitems, hi
 // (device routing; `queues` set, `nblocks` persistent workgroups drain the bucket queues).
 rs_status attn_launch_list(const rs_qkv *qkv, float scale, int fam, const rs_index_set *idx,
                            const DevUnit *d_units, const int *d_order, const AttnQueues *queues, int nblocks,
-                           void *o, int64_t so_h, int64_t so_t, float *lse, hipStream_t st) {
+                           const AttnParts &parts, void *o, int64_t so_h, int64_t so_t, float *lse, hipStream_t st) {
   if (nblocks <= 0) return RS_OK;
   AttnArgs a{};
   a.q = qkv->q; a.k = qkv->k; a.v = qkv->v;
@@ -1043,7 +1217,7 @@ rs_status attn_launch_list(const rs_qkv *qkv, float scale, int fam, const rs_ind
   a.sv_h = qkv->sv_h; a.sv_t = qkv->sv_t;
   a.o = (bf16 *)o; a.so_h = so_h; a.so_t = so_t; a.lse = lse;
   a.n = qkv->n; a.group = qkv->hq / qkv->hkv; a.scale = scale; a.c = scale * kLog2e;
-  a.units = d_units; a.order = d_order;
+  a.units = d_units; a.order = d_order; a.parts = parts;
   a.vt = (const bf16 *)qkv->vt; a.npad = (qkv->n + 63) / 64 * 64;
   if (queues) { a.qsize = queues->size; a.qoff = queues->off; a.qcount = queues->count; }
   if (fam == RS_VSLASH) {
@@ -1071,28 +1245,53 @@ rs_status attn_launch(const rs_qkv *qkv, float scale, const rs_unit *units, int3
   const int group = qkv->hq / qkv->hkv;
   std::vector<int> mate(nunits, -1), order;
   if (fam == RS_BSPARSE) pair_units(units, nunits, group, mate);
-  build_order(units, nunits, group, bm, mate, order);
-  const size_t need = attn_ws_bytes(units, nunits);
-  if (!ws || ws_bytes < need)
-    return fail(RS_ERR_WORKSPACE, "attention workspace too small: need " + std::to_string(need) +
+  // items split along the keys, where the workspace holds their partial results too
+  std::vector<SplitRule> split(nunits, SplitRule{1, 1});
+  size_t slots = 0;
+  for (int u = 0; u < nunits; ++u) {
+    split[u] = attn_split(qkv->hq, qkv->d, units[u].s0, units[u].s1, fam);
+    if (split[u].nsplit > 1) slots += (size_t)tiles_of(units[u], bm) * split[u].nsplit;
+  }
+  build_order(units, nunits, group, bm, mate, split, order);
+  size_t lbytes = attn_list_bytes(nunits, order.size());
+  if (slots > 0 && (!ws || ((uintptr_t)ws & 15) || ws_bytes < lbytes + attn_parts_bytes(qkv->d, slots))) {
+    slots = 0;
+    std::fill(split.begin(), split.end(), SplitRule{1, 1});
+    build_order(units, nunits, group, bm, mate, split, order);
+    lbytes = attn_list_bytes(nunits, order.size());
+  }
+  if (!ws || ws_bytes < lbytes)
+    return fail(RS_ERR_WORKSPACE, "attention workspace too small: need " + std::to_string(lbytes) +
                                       " bytes, got " + std::to_string(ws_bytes));
-  // host staging: [DevUnit x nunits][order]
+  AttnParts parts{};
+  if (slots > 0) parts = attn_parts_at((char *)ws + lbytes / 256 * 256, qkv->d, slots);  // past the list's end
+  // host staging: [DevUnit x nunits][order], and the split items by partial slot
   Arena ar(ws, ws_bytes);
   DevUnit *d_units = ar.take<DevUnit>((size_t)nunits);
   int *d_order = ar.take<int>(order.size());
   const size_t off_order = (char *)d_order - (char *)ws;
   std::vector<char> stage(off_order + order.size() * sizeof(int));
+  std::vector<int> items(slots, -1);
   DevUnit *h_units = (DevUnit *)stage.data();
+  int pbase = 0;
   for (int u = 0; u < nunits; ++u) {
+    const int ns = split[u].nsplit;
     h_units[u] = DevUnit{units[u].head, units[u].s0, units[u].s1, cand_local, units[u].slot,
                          fam == RS_ASHAPE ? cand->a : 0, fam == RS_ASHAPE ? cand->b : 0,
-                         mate[u] >= 0 ? units[mate[u]].head + 1 : 0, cand_local};
+                         mate[u] >= 0 ? units[mate[u]].head + 1 : 0, cand_local, ns, split[u].ptiles, pbase};
+    if (ns > 1)
+      for (int t = 0; t < tiles_of(units[u], bm); ++t, pbase += ns) items[pbase] = (u << 16) | t;
   }
   memcpy(stage.data() + off_order, order.data(), order.size() * sizeof(int));
   RS_HIP(hipMemcpyAsync(ws, stage.data(), stage.size(), hipMemcpyHostToDevice, st));
+  if (slots > 0)
+    RS_HIP(hipMemcpyAsync(parts.items, items.data(), items.size() * sizeof(int), hipMemcpyHostToDevice, st));
 
-  return attn_launch_list(qkv, scale, fam, idx, d_units, d_order, nullptr, (int)order.size(), o, so_h, so_t, lse,
-                          st);
+  rs_status rc = attn_launch_list(qkv, scale, fam, idx, d_units, d_order, nullptr, (int)order.size(), parts, o, so_h,
+                                  so_t, lse, st);
+  if (rc == RS_OK && slots > 0)
+    rc = attn_merge_launch(qkv, scale, d_units, parts, (int)slots, o, so_h, so_t, lse, st);
+  return rc;
 }
 
 }  // namespace rs

@@ -54,7 +54,59 @@ struct DevUnit {
   // block-sparse: head + 1 of a second unit (same rows, same key/value head) whose query
   // blocks this unit's items also run, and that unit's cl; 0: none (items of 128 rows)
   int mate, mate_cl;
+  // key splits of the unit's items (attn_split) and the unit's first partial slot: item t, piece p
+  // writes slot pbase + t * nsplit + p
+  int nsplit, ptiles, pbase;
 };
+
+// How the items (128-row query tiles) of one unit are split along the keys: at most nsplit pieces
+// of at least ptiles 64-key tiles, each a workgroup of its own, merged by attn_merge_kernel.  The
+// rule sees the unit and the layer's shape only, never the rest of the launch, so that a unit's
+// result does not depend on the units it is launched with.
+//   * The chip holds 512 workgroups of the attention kernel.  Dense items of all heads over the
+//     unit's rows that would leave more than half of them idle are split until they fill them
+//     (512 rows x 32 heads at 64K keys: 1195 us in one piece, 531 us in four).
+//   * Vertical-slash items have very different lengths (a diffuse head keeps several times the tiles
+//     of a local one), so they are split below four rounds of workgroups (2048 rows x 32 heads at
+//     50K keys: 1759 -> 1275 us with up to four pieces and the mask words fetched once per wave,
+//     which alone gives 1.17x).
+//   * A piece writes and the merge reads d + 2 floats per row: pieces are long enough (32 and 64
+//     tiles) to make that small, or 8 tiles where all partial results together stay in cache.
+// A-shape lists are short and block-sparse ones are even: neither is split.
+struct SplitRule {
+  int nsplit, ptiles;
+};
+constexpr int kMaxSplit = 16;
+__host__ __device__ inline SplitRule attn_split(int hq, int d, int s0, int s1, int fam) {
+  if (fam != RS_DENSE && fam != RS_VSLASH) return SplitRule{1, 1};
+  const int par = hq * ((s1 - 1) / 128 - s0 / 128 + 1);  // items of the unit's rows over all heads
+  int want = (fam == RS_DENSE ? 512 : 2048) / par;
+  want = want < kMaxSplit ? want : kMaxSplit;
+  if (want < 2) return SplitRule{1, 1};
+  const bool small = (long long)hq * (s1 - s0) * d * 4 * want <= 16ll << 20;
+  const int ptiles = small ? 8 : fam == RS_DENSE ? 32 : 64, most = ((s1 + 63) / 64) / ptiles;
+  const int n = want < most ? want : most;
+  return SplitRule{n < 1 ? 1 : n, ptiles};
+}
+// Partial slots (one per item and piece) of a unit, whatever its family turns out to be; 0 when it
+// never splits.
+__host__ __device__ inline int attn_split_slots(int hq, int d, int s0, int s1) {
+  const int a = attn_split(hq, d, s0, s1, RS_DENSE).nsplit, b = attn_split(hq, d, s0, s1, RS_VSLASH).nsplit;
+  const int m = a > b ? a : b;
+  return m > 1 ? m * ((s1 - 1) / 128 - s0 / 128 + 1) : 0;
+}
+// Partial results of split items.  Per slot and row of the item: O (fp32, unnormalised), running max
+// and sum; n: the pieces taken, at an item's first slot; items: per first slot the item
+// (unit << 16 | query tile), -1 elsewhere.
+struct AttnParts {
+  float *o, *ml;
+  int *n, *items;
+};
+size_t attn_parts_bytes(int d, size_t slots);
+AttnParts attn_parts_at(void *p, int d, size_t slots);
+// Merges the pieces of every split item.
+rs_status attn_merge_launch(const rs_qkv *qkv, float scale, const DevUnit *d_units, const AttnParts &parts,
+                            int slots, void *o, int64_t so_h, int64_t so_t, float *lse, hipStream_t st);
 
 // Device work queues of a persistent attention launch: per key/value bucket b (8), the items
 // order[off[b] .. off[b] + size[b]) and a counter of items taken (starts at 0).
@@ -66,7 +118,7 @@ struct AttnQueues {
 // One launch of a family's attention kernel over a device work list (attn.hip).
 rs_status attn_launch_list(const rs_qkv *qkv, float scale, int fam, const rs_index_set *idx,
                            const DevUnit *d_units, const int *d_order, const AttnQueues *queues, int nblocks,
-                           void *o, int64_t so_h, int64_t so_t, float *lse, hipStream_t st);
+                           const AttnParts &parts, void *o, int64_t so_h, int64_t so_t, float *lse, hipStream_t st);
 
 // bump allocator over a caller workspace
 struct Arena {

@@ -492,6 +492,8 @@ struct PlanArgs {
   int *order;       // [4][max_items], bucket-major
   int max_items;
   int *qsize, *qoff, *qcount;  // [4][8] each
+  int hq, d;
+  int *items;  // split items by partial slot (AttnParts::items), or NULL: no item is split
 };
 
 // Exclusive prefix sum over the workgroup (1024 threads) in thread order; *tot: the sum.
@@ -519,8 +521,8 @@ __device__ __forceinline__ int block_excl_scan(int v, int *sWave, int *tot) {
 // One workgroup per (family, key/value bucket), each on its own queue: units compacted by scans,
 // mates and item ranks searched among the bucket's units only.  Bound by latency; one workgroup
 // per family with serial passes over the units took 233 us for 256 units of 128 tiles, this 21 us.
-// Queue b of a family starts at the number of 128-row tiles of every unit of the buckets before
-// it (whatever their families), so that no workgroup needs another's counts; dunits is indexed by
+// Queue b of a family starts at the most items that the units of the buckets before it can have
+// (whatever their families), so that no workgroup needs another's counts; dunits is indexed by
 // the unit itself.
 __global__ void __launch_bounds__(1024) plan_kernel(const PlanArgs a) {
   const int f = blockIdx.x >> 3, b = blockIdx.x & 7, tid = threadIdx.x, NT = blockDim.x;
@@ -530,22 +532,34 @@ __global__ void __launch_bounds__(1024) plan_kernel(const PlanArgs a) {
   __shared__ int sOff[kRouteMaxUnits];   // first flat item
   // items of a unit: n of them, the j-th starting at row 64 (k0 + (j << sh)); sh = 1 for 128-row
   // query tiles, 0 for the 64-row query blocks of a block-sparse unit with a mate
-  __shared__ uint32_t sIt[kRouteMaxUnits];  // k0 | n << 13 | sh << 26
+  // (each split into sp pieces, dense and vertical-slash)
+  __shared__ uint32_t sIt[kRouteMaxUnits];  // k0 | n << 13 | sh << 26 | sp << 27
+  __shared__ int sPb[kRouteMaxUnits];       // first partial slot of the unit
   __shared__ int sWave[16];
   const int U = a.U;
-  int nl = 0, before = 0;
+  int nl = 0, before = 0, slots = 0;
   for (int u0 = 0; u0 < U; u0 += NT) {
     const int u = u0 + tid;
-    bool mine = false;
-    int tiles = 0;
+    bool mine = false, lost = false;
+    int tiles = 0, ps = 0;
     rs_unit un{};
     if (u < U) {
       un = a.units[u];
       const int c = a.choice[u], bu = (un.head / a.group) & 7;
-      mine = bu == b && c >= 0 && c < a.C && a.fam[c] == f;
-      tiles = bu < b ? ((un.s1 - 1) >> 7) - (un.s0 >> 7) + 1 : 0;
+      const bool valid = c >= 0 && c < a.C;
+      mine = bu == b && valid && a.fam[c] == f;
+      lost = bu == b && !valid && f == RS_DENSE;  // not computed: its partial slots hold no item
+      // query tiles in the buckets before this one, as many times as any family may split them
+      if (a.items) ps = attn_split_slots(a.hq, a.d, un.s0, un.s1);
+      tiles = bu < b ? max(((un.s1 - 1) >> 7) - (un.s0 >> 7) + 1, ps) : 0;
     }
-    int tot;
+    int tot, pb = 0;
+    if (a.items) {
+      pb = slots + block_excl_scan(ps, sWave, &tot);
+      slots += tot;
+      if (lost)
+        for (int x = 0; x < ps; ++x) a.items[pb + x] = -1;
+    }
     const int at = nl + block_excl_scan(mine ? 1 : 0, sWave, &tot);
     if (mine) {
       sU[at] = u;
@@ -553,6 +567,7 @@ __global__ void __launch_bounds__(1024) plan_kernel(const PlanArgs a) {
       sS0[at] = un.s0;
       sS1[at] = un.s1;
       sMate[at] = -1;
+      sPb[at] = pb;
     }
     nl += tot;
     block_excl_scan(tiles, sWave, &tot);
@@ -593,11 +608,20 @@ __global__ void __launch_bounds__(1024) plan_kernel(const PlanArgs a) {
       const int u = sU[x], c = a.choice[u], m = sMate[x];
       const int sh = m >= 0 ? 0 : 1, lg = 6 + sh;  // log2 of an item's rows
       n = m == -2 ? 0 : ((sS1[x] - 1) >> lg) - (sS0[x] >> lg) + 1;
-      sIt[x] = (uint32_t)((sS0[x] >> lg) << sh) | ((uint32_t)n << 13) | ((uint32_t)sh << 26);
+      const SplitRule sp = a.items ? attn_split(a.hq, a.d, sS0[x], sS1[x], f) : SplitRule{1, 1};
+      sIt[x] = (uint32_t)((sS0[x] >> lg) << sh) | ((uint32_t)n << 13) | ((uint32_t)sh << 26) |
+               ((uint32_t)sp.nsplit << 27);
+      if (a.items) {
+        const int ps = attn_split_slots(a.hq, a.d, sS0[x], sS1[x]);
+        for (int y = 0; y < ps; ++y)
+          a.items[sPb[x] + y] = sp.nsplit > 1 && y % sp.nsplit == 0 && y / sp.nsplit < n
+                                    ? ((f * U + u) << 16) | (y / sp.nsplit) : -1;
+      }
+      n *= sp.nsplit;
       if (n > 0)
         dunits[u] = DevUnit{sHead[x], sS0[x], sS1[x], a.cl[c], a.units[u].slot, f == RS_ASHAPE ? a.ca[c] : 0,
                             f == RS_ASHAPE ? a.cb[c] : 0, m >= 0 ? sHead[m] + 1 : 0,
-                            m >= 0 ? a.cl[a.choice[sU[m]]] : 0};
+                            m >= 0 ? a.cl[a.choice[sU[m]]] : 0, sp.nsplit, sp.ptiles, sPb[x]};
     }
     int tot;
     const int off = total + block_excl_scan(n, sWave, &tot);
@@ -618,25 +642,23 @@ __global__ void __launch_bounds__(1024) plan_kernel(const PlanArgs a) {
       if (sOff[mid] <= i) lo = mid;
       else hi = mid - 1;
     }
-    const int t = i - sOff[lo];
-    const int key = (int)(sIt[lo] & 0x1fffu) + (t << (sIt[lo] >> 26));  // first row / 64
-    // rank in the bucket: later query rows first, then units ascending
+    const int spl = (int)(sIt[lo] >> 27), j = i - sOff[lo], t = spl == 1 ? j : j / spl, piece = j - t * spl;
+    const int key = (int)(sIt[lo] & 0x1fffu) + (t << ((sIt[lo] >> 26) & 1u));  // first row / 64
+    // rank in the bucket: later query rows first, then units ascending, then pieces
     int r = 0;
     for (int x = 0; x < nl; ++x) {
       const uint32_t it = sIt[x];
-      const int n = (int)(it >> 13) & 0x1fff, sh = (int)(it >> 26);
+      const int n = (int)(it >> 13) & 0x1fff, sh = (int)(it >> 26) & 1, sp = (int)(it >> 27);
       const int d = key - (int)(it & 0x1fffu);
       const int below = d < 0 ? 0 : min(n, (d >> sh) + 1);  // items of x starting at or before key
-      r += n - below;
-      r += (x < lo && d >= 0 && (d & sh) == 0 && (d >> sh) < n) ? 1 : 0;
+      r += (n - below) * sp;
+      r += (x < lo && d >= 0 && (d & sh) == 0 && (d >> sh) < n) ? sp : 0;
     }
-    order[r] = (sU[lo] << 16) | t;
+    order[r + piece] = (sU[lo] << 16) | (piece << 12) | t;
   }
 }
 
 // ---- host launchers ----------------------------------------------------------------------
-static int tiles128(const rs_unit &u) { return (u.s1 - 1) / 128 - u.s0 / 128 + 1; }
-
 rs_status error_predict_launch(const rs_probe_out *p, const rs_candidate *grid, int32_t ncand,
                                const rs_error_model *m, float *e, hipStream_t st) {
   EpArgs a{};
@@ -729,15 +751,33 @@ rs_status route_dev_launch_noalloc(const rs_route_in *in, const rs_route_cfg *cf
   return route_run(in, cfg, out, fam, brank, dense_c, st);
 }
 
-size_t routed_attn_ws_bytes(const rs_unit *units, int32_t nunits) {
-  size_t items = 0;
-  for (int i = 0; i < nunits; ++i) items += (size_t)tiles128(units[i]);
+// Bytes of the work lists for at most `items` items per family.
+static size_t routed_list_bytes(int32_t nunits, size_t items) {
   Arena ar(nullptr, 0);
   ar.take<rs_unit>((size_t)nunits);
   ar.take<int>(3 * 32);
   ar.take<DevUnit>(4 * (size_t)nunits);
   ar.take<int>(4 * items);
-  return ar.off + 256;
+  return ar.off + 256;  // (rounded down to 256 bytes: at or past the lists' end)
+}
+
+// Most items of a family and partial slots of the units; split: items may be split along the keys.
+static void routed_counts(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, bool split, size_t *items,
+                          size_t *slots) {
+  *items = *slots = 0;
+  for (int i = 0; i < nunits; ++i) {
+    const rs_unit &u = units[i];
+    const int s = split && qkv && qkv->hq > 0 && u.s0 >= 0 && u.s1 > u.s0
+                      ? attn_split_slots(qkv->hq, qkv->d, u.s0, u.s1) : 0;
+    *items += (size_t)std::max((u.s1 - 1) / 128 - u.s0 / 128 + 1, s);
+    *slots += (size_t)s;
+  }
+}
+
+size_t routed_attn_ws_bytes(const rs_qkv *qkv, const rs_unit *units, int32_t nunits) {
+  size_t items, slots;
+  routed_counts(qkv, units, nunits, true, &items, &slots);
+  return routed_list_bytes(nunits, items) + attn_parts_bytes(qkv ? qkv->d : 0, slots);
 }
 
 rs_status routed_attn_launch(const rs_qkv *qkv, float scale, const rs_unit *units, int32_t nunits,
@@ -746,11 +786,18 @@ rs_status routed_attn_launch(const rs_qkv *qkv, float scale, const rs_unit *unit
                              void *const *events, hipStream_t st) {
   if (nunits == 0) return RS_OK;
   if (nunits > kRouteMaxUnits) return fail(RS_ERR_UNSUPPORTED, "routed attention supports nunits <= 2048");
-  const size_t need = routed_attn_ws_bytes(units, nunits);
+  size_t items, slots;
+  routed_counts(qkv, units, nunits, true, &items, &slots);
+  size_t need = routed_list_bytes(nunits, items);
+  // items are split where the workspace holds their partial results
+  if (slots > 0 && (!ws || ((uintptr_t)ws & 15) || ws_bytes < need + attn_parts_bytes(qkv->d, slots))) {
+    routed_counts(qkv, units, nunits, false, &items, &slots);
+    need = routed_list_bytes(nunits, items);
+  }
   if (!ws || ws_bytes < need)
     return fail(RS_ERR_WORKSPACE, "routed attention workspace too small: need " + std::to_string(need) + " bytes");
-  int items = 0;
-  for (int i = 0; i < nunits; ++i) items += tiles128(units[i]);
+  AttnParts parts{};
+  if (slots > 0) parts = attn_parts_at((char *)ws + need / 256 * 256, qkv->d, slots);
   Arena ar(ws, ws_bytes);
   rs_unit *d_units = ar.take<rs_unit>((size_t)nunits);
   int *d_q = ar.take<int>(3 * 32);
@@ -770,8 +817,11 @@ rs_status routed_attn_launch(const rs_qkv *qkv, float scale, const rs_unit *unit
   p.units = d_units;
   p.choice = choice;
   p.dunits = ar.take<DevUnit>(4 * (size_t)nunits);
-  p.order = ar.take<int>(4 * (size_t)items);
-  p.max_items = items;
+  p.order = ar.take<int>(4 * items);
+  p.max_items = (int)items;
+  p.hq = qkv->hq;
+  p.d = qkv->d;
+  p.items = slots > 0 ? parts.items : nullptr;
   p.qsize = d_q;
   p.qoff = d_q + 32;
   p.qcount = d_q + 64;
@@ -787,7 +837,7 @@ rs_status routed_attn_launch(const rs_qkv *qkv, float scale, const rs_unit *unit
   int dev = 0, ncu = 0;
   RS_HIP(hipGetDevice(&dev));
   RS_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
-  const int nblocks = std::min(((2 * ncu + 7) / 8) * 8, ((items + 7) / 8) * 8);
+  const int nblocks = std::min(((2 * ncu + 7) / 8) * 8, (((int)items + 7) / 8) * 8);
   // dense first: its tiles are the longest
   const int fam_order[4] = {RS_DENSE, RS_VSLASH, RS_BSPARSE, RS_ASHAPE};
   if (events) RS_HIP(hipEventRecord((hipEvent_t)events[0], st));
@@ -796,7 +846,11 @@ rs_status routed_attn_launch(const rs_qkv *qkv, float scale, const rs_unit *unit
     if (present[f]) {
       const AttnQueues qs{p.qsize + 8 * f, p.qoff + 8 * f, p.qcount + 8 * f};
       rs_status s = attn_launch_list(qkv, scale, f, idx, p.dunits + (size_t)f * nunits,
-                                     p.order + (size_t)f * items, &qs, nblocks, o, so_h, so_t, lse, st);
+                                     p.order + (size_t)f * items, &qs, nblocks, parts, o, so_h, so_t, lse, st);
+      if (s != RS_OK) return s;
+    }
+    if (f == RS_VSLASH && slots > 0) {  // the two families with split items are launched
+      rs_status s = attn_merge_launch(qkv, scale, p.dunits, parts, (int)slots, o, so_h, so_t, lse, st);
       if (s != RS_OK) return s;
     }
     if (events) RS_HIP(hipEventRecord((hipEvent_t)events[1 + k], st));
