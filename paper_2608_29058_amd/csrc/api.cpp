@@ -116,7 +116,7 @@ rs_status attn_launch(const rs_qkv *qkv, float scale, const rs_unit *units, int3
 size_t unit_table_bytes(int32_t nunits, const rs_probe_cfg *cfg);
 rs_status unit_table_init(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, const rs_probe_cfg *cfg,
                           void *dev, size_t bytes, rs_unit_table *out, hipStream_t st);
-size_t probe_ws_bytes(const rs_qkv *qkv, int32_t nunits, const rs_probe_cfg *cfg);
+size_t probe_ws_bytes(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, const rs_probe_cfg *cfg);
 rs_status probe_launch(const rs_qkv *qkv, float scale, const rs_unit *units, int32_t nunits,
                        const rs_probe_cfg *cfg, const rs_candidate *grid, int32_t ncand, const rs_index_set *idx,
                        void *ws, size_t ws_bytes, rs_probe_out *out, hipStream_t st);
@@ -264,9 +264,8 @@ rs_status rs_unit_table_init(const rs_qkv *qkv, const rs_unit *units, int32_t nu
 }
 
 size_t rs_probe_workspace_size(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, const rs_probe_cfg *cfg) {
-  (void)units;
   if (!qkv || !cfg || nunits < 0) return 0;
-  return probe_ws_bytes(qkv, nunits, cfg);
+  return probe_ws_bytes(qkv, units, nunits, cfg);
 }
 
 rs_status rs_probe(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, const rs_probe_cfg *cfg,

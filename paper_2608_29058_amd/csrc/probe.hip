@@ -25,7 +25,9 @@
 namespace rs {
 
 constexpr int kProbeMaxRows = 256;  // sampled rows per unit
-constexpr int kRange = 1024;        // keys per workgroup range in the three passes
+// keys per workgroup range in the three passes: a power of two in [kMinRange, kMaxRange]
+// (probe_range), in an order that halves a launch's serial tiles where it would not fill the chip
+constexpr int kMinRange = 128, kMaxRange = 1024;
 constexpr int kMaxCand = 16;
 constexpr int kPrefVs = 3;   // vertical-slash candidates whose bitmap words are prefetched
 constexpr int kPrefBs = 3;   // block-sparse candidates whose selection words are prefetched
@@ -46,6 +48,7 @@ struct ProbeArgs {
   const void *q, *k;
   long long sq_h, sq_t, sk_h, sk_t;
   int n, group, rmax, nchunks;
+  int range, rsh;            // keys per range and its log2; nchunks ranges
   int lg_groups, lg_pairs;  // task grid of a range pass: unit groups x row-block pairs per range
   float c, scale;
   int local_w;
@@ -57,7 +60,7 @@ struct ProbeArgs {
   float *col, *diag_part, *ent_part, *loc_part;
   float *max_part, *sum_part;  // coverage pass: per (row, range) running max and sum
   int stats_rows;              // rows (from the end of the row list) the statistics pass covers
-  int diag_w;  // width of a diagonal partial row (kRange + rmax)
+  int diag_w;  // width of a diagonal partial row (range + rmax)
   // pass 3
   int ncand;
   CandDev cand[kMaxCand];
@@ -212,7 +215,7 @@ __global__ void __launch_bounds__(256, 2) probe_range_kernel(const ProbeArgs a) 
   // tile's copy can be issued at the start of the current tile
   __shared__ __align__(16) bf16 sK0[TE];
   __shared__ __align__(16) bf16 sK1[NKB == 2 ? TE : 8];
-  __shared__ int sRows[2][32];
+  __shared__ int sRowsA[4][2][32];  // per wave: the rows of its pair
   // coverage pass: per wave (unit) and prefetched vertical-slash candidate, the diagonal-bitmap
   // words that the windows of this row-block pair and key range read (staged when they fit)
   constexpr int kDCap = MODE == M_COVER ? 576 : 1;
@@ -223,23 +226,29 @@ __global__ void __launch_bounds__(256, 2) probe_range_kernel(const ProbeArgs a) 
   if (rg >= a.nchunks) return;
   const int4 grp = a.groups[task.gy];
   const ProbeUnit U0 = a.units[grp.x];
-  const int c0 = rg * kRange;
+  const int c0 = rg << a.rsh;
   if (c0 >= U0.s1) return;
-  const int kend = min(c0 + kRange, U0.s1);
+  const int kend = min(c0 + a.range, U0.s1);
   const int nrows = U0.nrows, nrb = (nrows + 31) / 32;
-  int p_lo, p_hi;
+  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  int p_lo, p_hi, uw = wave;  // this wave's row-block pairs and its unit within the group
   if constexpr (MODE == M_SCORES) {
     if (U0.nR <= 0) return;
     p_lo = 0;
     p_hi = (U0.nR - 1) / 64 + 1;
   } else {
-    p_lo = task.pz;
+    // the group's (unit, pair) tasks in turn over the waves: with 4 units a wave per unit and a
+    // pair per workgroup, with fewer the waves take further pairs (head counts per key/value head
+    // that are no multiple of four, a single head)
+    const int gsz = 1 + (grp.y >= 0) + (grp.z >= 0) + (grp.w >= 0), t = 4 * task.pz + wave;
+    if (4 * task.pz >= gsz * a.lg_pairs) return;
+    p_lo = t / gsz;
     p_hi = p_lo + 1;
-    if (2 * p_lo >= nrb) return;
+    uw = t - p_lo * gsz;
+    if (p_lo >= a.lg_pairs || 2 * p_lo >= nrb) uw = 4;  // this wave only copies
   }
-  const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, hh = lane >> 5;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int u = wave == 0 ? grp.x : wave == 1 ? grp.y : wave == 2 ? grp.z : grp.w;
+  const int u = uw == 0 ? grp.x : uw == 1 ? grp.y : uw == 2 ? grp.z : uw == 3 ? grp.w : -1;
   const InT *Kp = (const InT *)a.k + (long long)(U0.head / a.group) * a.sk_h;
 
   // K tile copies: per-lane byte offset fixed, the tile's first key as a scalar offset
@@ -274,16 +283,16 @@ __global__ void __launch_bounds__(256, 2) probe_range_kernel(const ProbeArgs a) 
   // partials of this range, all in LDS
   float (*sD)[kSkew] = nullptr;
   float *sCol = nullptr, *sDg = nullptr;
-  const int dw = kRange + U0.nR;                // diagonals touched by recent rows in this range
-  const int dbase = U0.r0 - (c0 + kRange - 1);  // smallest such diagonal
+  const int dw = a.range + U0.nR;                // diagonals touched by recent rows in this range
+  const int dbase = U0.r0 - (c0 + a.range - 1);  // smallest such diagonal
   if constexpr (MODE == M_SCORES) {
     __shared__ float sDbuf[4][16][kSkew];
-    __shared__ float sColbuf[4][kRange];
-    __shared__ float sDgbuf[4][kRange + kProbeMaxRows];
+    __shared__ float sColbuf[4][kMaxRange];
+    __shared__ float sDgbuf[4][kMaxRange + kProbeMaxRows];
     sD = sDbuf[wave];
     sCol = sColbuf[wave];
     sDg = sDgbuf[wave];
-    for (int x = lane; x < kRange; x += 64) sCol[x] = 0.f;
+    for (int x = lane; x < a.range; x += 64) sCol[x] = 0.f;
     for (int x = lane; x < dw; x += 64) sDg[x] = 0.f;
     for (int x = lane; x < 16 * kSkew; x += 64) sD[x / kSkew][x % kSkew] = 0.f;
   }
@@ -296,15 +305,17 @@ __global__ void __launch_bounds__(256, 2) probe_range_kernel(const ProbeArgs a) 
   for (int pr = p_lo; pr < p_hi; ++pr) {
     // ---- the pair's two blocks: rows, Q fragments, per-row constants ------------------------
     const int b1 = nrb - 1 - 2 * pr, b0 = b1 - 1;
+    int (*sRows)[32] = sRowsA[wave];
     __syncthreads();  // previous pair done with sRows and the tile buffers
-    if (tid < 64) {
-      const int s = tid >> 5, b = s ? b1 : b0;
-      const int x = nrows - 32 * (nrb - b) + (tid & 31);
-      sRows[s][tid & 31] = (b >= 0 && x >= 0) ? a.rows[(long long)grp.x * a.rmax + x] : -1;
+    {
+      const int s = lane >> 5, b = s ? b1 : b0;
+      const int x = nrows - 32 * (nrb - b) + l32;
+      sRows[s][l32] = (u >= 0 && b >= 0 && x >= 0) ? a.rows[(long long)grp.x * a.rmax + x] : -1;
     }
     __syncthreads();
     const int rmax0 = sRows[0][31], rmax1 = sRows[1][31];  // rows ascending; -1: no block
-    const int kstop = min(kend, rmax1 + 1);                 // keys beyond the last row are unseen
+    // keys beyond the last row of any wave are unseen
+    const int kstop = min(kend, max(max(sRowsA[0][1][31], sRowsA[1][1][31]), max(sRowsA[2][1][31], sRowsA[3][1][31])) + 1);
     if (kstop <= c0) continue;                              // uniform over the workgroup
     const int nt = (kstop - c0 + 63) >> 6;
 
@@ -371,10 +382,10 @@ __global__ void __launch_bounds__(256, 2) probe_range_kernel(const ProbeArgs a) 
       for (int s = 0; s < 2; ++s)
         if (row[s] >= 0) rlo = min(rlo, row[s]);
 #pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) rlo = min(rlo, __shfl_xor(rlo, o));  // the last block has rows
-      dw0 = (rlo - c0 - (kRange - 1)) >> 5;
+      for (int o = 32; o >= 1; o >>= 1) rlo = min(rlo, __shfl_xor(rlo, o));  // an active wave's last block has rows
+      dw0 = (rlo - c0 - (a.range - 1)) >> 5;
       const int nspan = ((rmax1 - c0 - 63) >> 5) + 3 - dw0;
-      stage = nspan <= kDCap;  // the same rows for every wave
+      stage = u >= 0 && nspan <= kDCap;
 #pragma unroll
       for (int s = 0; s < 2; ++s)
 #pragma unroll
@@ -772,7 +783,7 @@ __global__ void __launch_bounds__(256, 2) probe_range_kernel(const ProbeArgs a) 
   if constexpr (MODE == M_SCORES) {
     __syncthreads();
     if (u >= 0) {
-      for (int x = lane; x < kRange; x += 64) {
+      for (int x = lane; x < a.range; x += 64) {
         const int j = c0 + x;
         if (j < a.n) a.col[(long long)u * a.n + j] = (j < U0.s1) ? sCol[x] : 0.f;
       }
@@ -803,7 +814,7 @@ __global__ void probe_stats_combine_kernel(const ProbeArgs a) {
   const int x = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (x >= U.nrows || x < U.nrows - a.stats_rows) return;
   const int row = a.rows[(long long)u * a.rmax + x];
-  const int nch = row / kRange + 1;
+  const int nch = (row >> a.rsh) + 1;
   const float *pm = a.ent_part + ((long long)u * a.rmax + x) * a.nchunks;
   const float *pl = a.loc_part + ((long long)u * a.rmax + x) * a.nchunks;
   float M = -INFINITY;
@@ -828,14 +839,14 @@ __global__ void probe_finish_kernel(const ProbeArgs a, float *diag, float *entro
   auto diag_at = [&](int x) -> float {
     float v = 0.f;
     if (x < U.s1 && U.nR > 0) {
-      // chunks whose diagonal range [r0 - c0 - (kRange-1), r0 + nR - 1 - c0] holds t = x
-      const int chi = min((U.r0 + U.nR - 1 - x) / kRange, (U.s1 - 1) / kRange);
-      const int clo_num = U.r0 - (kRange - 1) - x;
-      const int clo = clo_num <= 0 ? 0 : (clo_num + kRange - 1) / kRange;
+      // chunks whose diagonal range [r0 - c0 - (range - 1), r0 + nR - 1 - c0] holds t = x
+      const int chi = min((U.r0 + U.nR - 1 - x) >> a.rsh, (U.s1 - 1) >> a.rsh);
+      const int clo_num = U.r0 - (a.range - 1) - x;
+      const int clo = clo_num <= 0 ? 0 : (clo_num + a.range - 1) >> a.rsh;
       for (int ch = clo; ch <= chi; ++ch) {
-        const int dbase = U.r0 - (ch * kRange + kRange - 1);
+        const int dbase = U.r0 - ((ch << a.rsh) + a.range - 1);
         const int xi = x - dbase;
-        if (xi >= 0 && xi < kRange + U.nR) v += a.diag_part[((long long)u * a.nchunks + ch) * a.diag_w + xi];
+        if (xi >= 0 && xi < a.range + U.nR) v += a.diag_part[((long long)u * a.nchunks + ch) * a.diag_w + xi];
       }
     }
     return v;
@@ -878,7 +889,7 @@ __global__ void cover_combine_kernel(const ProbeArgs a, float *entropy, float *l
   const int x = blockIdx.x * 16 + (threadIdx.x >> 4), lane = threadIdx.x & 15;
   if (x >= U.nrows) return;  // the sixteen lanes of a row leave together
   const int row = a.rows[(long long)u * a.rmax + x];
-  const int nch = row / kRange + 1;
+  const int nch = (row >> a.rsh) + 1;
   const long long base = ((long long)u * a.rmax + x) * a.nchunks;
   const float *pm = a.max_part + base, *pz = a.sum_part + base;
   const float *pe = a.ent_part + base, *pl = a.loc_part + base;
@@ -1272,27 +1283,66 @@ rs_status unit_table_init(const rs_qkv *qkv, const rs_unit *units, int32_t nunit
   return RS_OK;
 }
 
-size_t probe_ws_bytes(const rs_qkv *qkv, int32_t nunits, const rs_probe_cfg *cfg) {
-  const int rmax = rmax_of(cfg);
-  const long long nchunks = (qkv->n + kRange - 1) / kRange;
-  const int nb = (qkv->n + 63) / 64;
-  Arena ar(nullptr, 0);
-  ar.take<ProbeUnit>(nunits);
-  ar.take<int4>(nunits);
-  ar.take<float>((size_t)nunits * nchunks * (kRange + rmax));     // diag partials
-  ar.take<float>((size_t)nunits * nchunks * rmax * 4);            // max / sum / entropy / local partials
-  ar.take<float>((size_t)nunits * nchunks * rmax * kMaxCand);     // coverage partials
-  if (cfg->flags & RS_PROBE_BLOCKMEAN) {
-    ar.take<float>((size_t)qkv->hq * nb * qkv->d);
-    ar.take<float>((size_t)qkv->hkv * nb * qkv->d);
+// Keys per range of a pass: 1024, halved while the launch would have fewer than `want` workgroups
+// (one per group of up to four units, range within the units' keys and, in the coverage pass, pair
+// of row blocks).  A workgroup takes its range's tiles one after the other, so a launch that does
+// not fill the 512 workgroups the chip holds takes as long as one range; once it fills most of
+// them, shorter ranges only add set-up and partial results.  Measured: scores pass of one head at
+// 2K, 2 workgroups: 52 us, 16: 16 us; 28 heads at 50K, 392 workgroups: 87 us, 1568: 104 us;
+// coverage pass of 32 heads at 8K in segments of 2048, 480 workgroups: 159 us, 960: 115 us.
+constexpr int kWantScores = 320, kWantCover = 640;
+static int probe_range(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, int pairs, int want) {
+  const int gsz = std::max(1, std::min(4, qkv->hq / qkv->hkv));
+  int r = kMaxRange;
+  for (; r > kMinRange; r >>= 1) {
+    long long wgs = 0;
+    for (int i = 0; i < nunits; ++i) wgs += ((units ? units[i].s1 : qkv->n) + r - 1) / r;
+    if (wgs * std::max(pairs, 1) >= (long long)want * gsz) break;
   }
-  return ar.off + 256;
+  return r;
+}
+
+static int row_pairs(int rows) { return ((rows + 31) / 32 + 1) / 2; }
+
+// Workspace of a scores call (coverage: of a coverage call) with ranges of `range` keys.
+struct ProbeWs {
+  ProbeUnit *units;
+  int4 *groups;
+  float *diag_part, *max_part, *sum_part, *ent_part, *loc_part, *cov_part, *qbar, *kbar;
+  size_t bytes;
+};
+static ProbeWs probe_ws_layout(void *ws, const rs_qkv *qkv, int32_t nunits, const rs_probe_cfg *cfg, int range) {
+  const int rmax = rmax_of(cfg), nb = (qkv->n + 63) / 64;
+  const long long nchunks = (qkv->n + range - 1) / range;
+  Arena ar(ws, ~size_t(0));
+  ProbeWs w{};
+  w.units = ar.take<ProbeUnit>(nunits);
+  w.groups = ar.take<int4>(nunits);
+  w.diag_part = ar.take<float>((size_t)nunits * nchunks * (range + rmax));
+  w.ent_part = ar.take<float>((size_t)nunits * nchunks * rmax);
+  w.loc_part = ar.take<float>((size_t)nunits * nchunks * rmax);
+  w.max_part = ar.take<float>((size_t)nunits * nchunks * rmax);
+  w.sum_part = ar.take<float>((size_t)nunits * nchunks * rmax);
+  w.cov_part = ar.take<float>((size_t)nunits * nchunks * rmax * kMaxCand);
+  if (cfg->flags & RS_PROBE_BLOCKMEAN) {
+    w.qbar = ar.take<float>((size_t)qkv->hq * nb * qkv->d);
+    w.kbar = ar.take<float>((size_t)qkv->hkv * nb * qkv->d);
+  }
+  w.bytes = ar.off + 256;
+  return w;
+}
+
+size_t probe_ws_bytes(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, const rs_probe_cfg *cfg) {
+  if (qkv->n < 1 || qkv->hq < 1 || qkv->hkv < 1) return 256;
+  const int r1 = probe_range(qkv, units, nunits, 1, kWantScores);
+  const int r2 = probe_range(qkv, units, nunits, row_pairs(rmax_of(cfg)), kWantCover);
+  return probe_ws_layout(nullptr, qkv, nunits, cfg, std::min(r1, r2)).bytes;
 }
 
 template <int D, typename InT>
 static hipError_t launch_rows(const ProbeArgs &pa, int nunits, int ngroups, int mode, float *diag, float *ent, float *loc,
                               float *cov_rows, float *cov, hipStream_t st) {
-  const int npairs = ((pa.rmax + 31) / 32 + 1) / 2;  // row-block pairs of the fullest unit
+  const int npairs = row_pairs(pa.rmax);  // row-block pairs of the fullest unit
   ProbeArgs ra = pa;  // with the task grid of each range pass
   ra.lg_groups = ngroups;
   if (mode == 0) {
@@ -1331,28 +1381,24 @@ rs_status probe_launch(const rs_qkv *qkv, float scale, const rs_unit *units, int
                        const rs_probe_cfg *cfg, const rs_candidate *grid, int32_t ncand,
                        const rs_index_set *idx, void *ws, size_t ws_bytes, rs_probe_out *out, hipStream_t st) {
   const int rmax = rmax_of(cfg);
-  const int nchunks = (qkv->n + kRange - 1) / kRange;
   const int nb = (qkv->n + 63) / 64;
-  const size_t need = probe_ws_bytes(qkv, nunits, cfg);
-  if (!ws || ws_bytes < need)
-    return fail(RS_ERR_WORKSPACE, "probe workspace too small: need " + std::to_string(need));
-  Arena ar(ws, ws_bytes);
-  ProbeUnit *d_units = ar.take<ProbeUnit>(nunits);
-  int4 *d_groups = ar.take<int4>(nunits);
-  float *diag_part = ar.take<float>((size_t)nunits * nchunks * (kRange + rmax));
-  float *ent_part = ar.take<float>((size_t)nunits * nchunks * rmax);
-  float *loc_part = ar.take<float>((size_t)nunits * nchunks * rmax);
-  float *max_part = ar.take<float>((size_t)nunits * nchunks * rmax);
-  float *sum_part = ar.take<float>((size_t)nunits * nchunks * rmax);
-  float *cov_part = ar.take<float>((size_t)nunits * nchunks * rmax * kMaxCand);
-  float *qbar = nullptr, *kbar = nullptr;
-  if (cfg->flags & RS_PROBE_BLOCKMEAN) {
-    qbar = ar.take<float>((size_t)qkv->hq * nb * qkv->d);
-    kbar = ar.take<float>((size_t)qkv->hkv * nb * qkv->d);
+  const bool cover = idx != nullptr;
+  // a workspace sized for longer ranges is used with those
+  int range = cover ? probe_range(qkv, units, nunits, row_pairs(rmax), kWantCover)
+                    : probe_range(qkv, units, nunits, 1, kWantScores);
+  ProbeWs w = probe_ws_layout(ws, qkv, nunits, cfg, range);
+  while (ws && ws_bytes < w.bytes && range < kMaxRange) {
+    range <<= 1;
+    w = probe_ws_layout(ws, qkv, nunits, cfg, range);
   }
+  if (!ws || ws_bytes < w.bytes)
+    return fail(RS_ERR_WORKSPACE, "probe workspace too small: need " + std::to_string(w.bytes));
+  const int nchunks = (qkv->n + range - 1) / range;
+  ProbeUnit *d_units = w.units;
+  int4 *d_groups = w.groups;
+  float *qbar = w.qbar, *kbar = w.kbar;
   // per-unit tables: read from the caller's unit table, or built here and uploaded into the
   // workspace (sampled rows to the probe output in scores mode)
-  const bool cover = idx != nullptr;
   const rs_unit_table *tab = qkv->tables;
   const ProbeUnit *pu_dev = d_units;
   const int4 *grp_dev = d_groups;
@@ -1393,10 +1439,11 @@ rs_status probe_launch(const rs_qkv *qkv, float scale, const rs_unit *units, int
     pa.nsub_tab = nsub_tab;
   }
   pa.row_max = out->row_max; pa.row_sum = out->row_sum;
-  pa.col = out->col; pa.diag_part = diag_part; pa.ent_part = ent_part; pa.loc_part = loc_part;
-  pa.max_part = max_part; pa.sum_part = sum_part;
-  pa.diag_w = kRange + rmax;
-  pa.cov_part = cov_part;
+  pa.range = range; pa.rsh = __builtin_ctz(range);
+  pa.col = out->col; pa.diag_part = w.diag_part; pa.ent_part = w.ent_part; pa.loc_part = w.loc_part;
+  pa.max_part = w.max_part; pa.sum_part = w.sum_part;
+  pa.diag_w = range + rmax;
+  pa.cov_part = w.cov_part;
   if (cover) {
     pa.ncand = ncand;
     int nvs = 0, nbs = 0;
