@@ -308,8 +308,8 @@ rs_status rs_route_layer_device_noalloc(const rs_route_in *in, const rs_route_cf
 
 /* ---- routed attention from a device route (Sec. 3.4 grouping, inference step 6) ---------
  * Runs every unit u with candidate choice[u] (device int32 [nunits], e.g.
- * rs_route_dev_out.choice): one launch per family present in the grid, each over all the
- * units routed to any budget of that family.
+ * rs_route_dev_out.choice): one launch for every family's items (with `events`, one launch per
+ * family present in the grid).
  *  - Work lists are built on the device by a planning kernel: query tiles bucketed by
  *    key/value head, longest first.
  *  - O and lse equal those of one rs_sparse_attn_prefill / rs_dense_attn_prefill call per

@@ -52,10 +52,10 @@ struct AttnArgs {
   int n, group;
   float c, scale;
   const DevUnit *units;
-  const int *order;   // items; with queues, bucket b's at order[qoff[b] .. qoff[b] + qsize[b])
-  const int *qsize;   // [8] items per key/value bucket (device), or NULL: one item per workgroup
-  const int *qoff;    // [8]
-  int *qcount;        // [8] items taken per bucket (device counters, start at 0)
+  const int *order;   // items; with queues, queue q's at order[qoff[q] .. qoff[q] + qsize[q])
+  const int *qsize;   // [4][8] items per family and key/value bucket (device), or NULL: one item per workgroup
+  const int *qoff;    // [4][8]
+  int *qcount;        // [4][8] items taken per queue (device counters, start at 0)
   const bf16 *vt;  // V^T layout of rs_transpose_v (used by the VT instantiations)
   int npad;
   const int *vs_vsorted, *vs_dsorted, *vs_count;
@@ -115,11 +115,28 @@ struct TileRef {
 // bit 2m of the result: either of bits 2m, 2m + 1 of w (64-key tile m of a word of 32-key halves)
 __device__ __forceinline__ uint32_t tile_bits(uint32_t w) { return (w | (w >> 1)) & 0x55555555u; }
 
+// LDS words of a pattern beside its tile buffers: bitmaps, gathered columns, scan.
+template <int PAT>
+struct AttnLds {
+  static constexpr int kX = PAT == P_VS ? kMaxTiles / 16 : PAT == P_BS ? 2 * (kMaxTiles / 32 + 1) : 1;
+  static constexpr int kG = PAT == P_VS ? kMaxGather : 1, kScan = PAT == P_VS ? 4 : 1;
+};
+// The LDS of a kernel.  K and V tiles are double-buffered separately (K runs one tile ahead of V),
+// row-major and swizzled.  Distinct arrays, declared by the kernel and seen as such once attn_item is
+// inlined, and a parity known at compile time let the compiler see that a copy in flight never
+// overlaps the tiles, bitmaps and columns being read.
+#define RS_ATTN_LDS(D, NX, NG, NS)                                                              \
+  __shared__ __align__(16) bf16 sK0[64 * (D)], sK1[64 * (D)], sV0[64 * (D)], sV1[64 * (D)];     \
+  __shared__ uint32_t sX[NX];                                                                   \
+  __shared__ int sG[NG], sScan[NS]
+
 // One work item: piece `item >> 12 & 15` of query tile `item & 0xfff` of unit `item >> 16` of the
 // launch's unit list.
 // VT: V is read from the transposed copy (tiles of D rows x 64 keys), else from V itself.
-template <int D, int PAT, typename InT, bool VT>
-__device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
+// sK0..sV1: the tile buffers; sX, sG, sScan: the pattern's LDS (AttnLds), all owned by the kernel.
+template <int D, int PAT, typename InT, bool VT, bool kLayer, typename Args>
+__device__ __forceinline__ void attn_item(const Args &a, const int item, bf16 *sK0, bf16 *sK1, bf16 *sV0,
+                                          bf16 *sV1, uint32_t *sX, int *sG, int *sScan) {
   constexpr int NW = 4, NT = 256, BM = 128;
   constexpr int KS = D / 16;             // k-steps of the QK^T contraction
   constexpr int DB = D / 32;             // 32-row blocks of O^T
@@ -137,20 +154,12 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
   // each K read right before its product unless the order is forced (scheduling groups)
   constexpr bool kForceOrder = PAT == P_VS || PAT == P_BS;
 
-  // K and V tiles are double-buffered separately (K runs one tile ahead of V), row-major and
-  // swizzled.  Four distinct arrays, addressed with a parity known at compile time, let the
-  // compiler see that a copy in flight never overlaps the tiles being read.
-  __shared__ __align__(16) bf16 sK0[TE];
-  __shared__ __align__(16) bf16 sK1[TE];
-  __shared__ __align__(16) bf16 sV0[TE];
-  __shared__ __align__(16) bf16 sV1[TE];
-
   // opaque: what the set-up and the epilogue derive from it is computed again for every item
   // instead of being kept in registers across a persistent workgroup's item loop, where
-  // vertical-slash (19 spilled registers) ran 9.0 instead of 6.2 ms on a routed 128K layer.  (Reading
-  // the arguments again per item as well saves scalar spills but costs dense 2%.)
+  // vertical-slash (19 spilled registers) ran 9.0 instead of 6.2 ms on a routed 128K layer, and the
+  // layer kernel spilled 40 (9 now).  Dense alone has the registers and is 0.5% faster without.
   int tid = threadIdx.x;
-  if constexpr (PAT == P_VS || PAT == P_BS) asm volatile("" : "+v"(tid));
+  if constexpr (PAT == P_VS || PAT == P_BS || kLayer) asm volatile("" : "+v"(tid));
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
@@ -196,20 +205,17 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
   // block-sparse: key blocks selected by query block bq (sBA) and bq + 1 (sBB) as bitmaps;
   // words for key blocks 0 .. bq + 1, where bq + 1 reaches kMaxTiles for the last 64-row item
   // of a sequence of the maximum length
-  __shared__ uint32_t sBA[PAT == P_BS ? kMaxTiles / 32 + 1 : 1], sBB[PAT == P_BS ? kMaxTiles / 32 + 1 : 1];
+  [[maybe_unused]] uint32_t *sBA = sX, *sBB = sX + kMaxTiles / 32 + 1;
   const uint32_t *vbits = nullptr, *dbits = nullptr;
   int n_contig = 0, n_gather = 0;
   [[maybe_unused]] int g_first = 0, n_gtiles = 0;  // vertical-slash: gathered tiles of this item's piece
   [[maybe_unused]] int t_first = 0;                // dense: first tile of this item's piece
   // vertical-slash: sTB, one bit per 32-key half of the key range the block's diagonals touch
   // (a 64-key tile is in the list when either of its halves is, and only those halves are
-  // copied); sG, the gathered vertical columns.  Arrays of their own, not pointers, so that
-  // the compiler sees them apart from the tiles being copied.
-  __shared__ uint32_t sTB[PAT == P_VS ? kMaxTiles / 16 : 1];
-  __shared__ int sG[PAT == P_VS ? kMaxGather : 1];
+  // copied); sG, the gathered vertical columns.
+  [[maybe_unused]] uint32_t *sTB = sX;
 
   if constexpr (PAT == P_VS) {
-    __shared__ int sScan[NW + 1];
     const long long vsrow = (long long)U.slot * a.ncand_vs + U.cl;
     const int *vsorted = a.vs_vsorted + vsrow * a.nv_max;
     const int *dsorted = a.vs_dsorted + vsrow * a.ns_max;
@@ -917,37 +923,72 @@ __device__ __forceinline__ void attn_item(const AttnArgs &a, const int item) {
     a.lse[(long long)whead * a.n + i] = l_tot > 0.f ? m_run * a.scale + logf(l_tot) : -INFINITY;
 }
 
-// attn_fwd_kernel: workgroup b runs item order[b].  attn_fwd_queue_kernel: the grid is
-// persistent; workgroup b (on XCD b % 8 under round-robin dispatch) takes the next item of the
-// queue of key/value bucket b % 8 (items there are longest first), then of the other buckets
-// once its own is empty, until every queue is drained.  Each queue counter starts at 0 (the
-// planner writes it) and is only ever incremented, so every workgroup reaches the exit.
+// attn_fwd_kernel: workgroup b runs item order[b].
 template <int D, int PAT, typename InT, bool VT>
 __global__ void __launch_bounds__(256, 2) attn_fwd_kernel(const AttnArgs a) {
-  attn_item<D, PAT, InT, VT>(a, a.order[blockIdx.x]);
+  RS_ATTN_LDS(D, AttnLds<PAT>::kX, AttnLds<PAT>::kG, AttnLds<PAT>::kScan);
+  attn_item<D, PAT, InT, VT, false>(a, a.order[blockIdx.x], sK0, sK1, sV0, sV1, sX, sG, sScan);
 }
 
-template <int D, int PAT, typename InT, bool VT>
-__global__ void __launch_bounds__(256, 2) attn_fwd_queue_kernel(const AttnArgs a) {
-  __shared__ int sItem;
-  const int x = (int)(blockIdx.x & 7u);
+// The persistent kernels take items from queues: family f's queue of key/value bucket b holds the
+// qsize[8 f + b] items at order[qoff[8 f + b]] (longest first) and a counter of items taken,
+// which starts at 0 (the planner writes it) and is only ever incremented, so an empty queue stays
+// empty and every workgroup reaches the exit.  Workgroup x (on XCD x % 8 under round-robin
+// dispatch) takes bucket x % 8 first, then the others.
+template <int D, int PAT, typename InT, bool VT, bool kLayer>
+__device__ __forceinline__ void drain_family(const AttnArgs &a, int *sItem, bf16 *sK0, bf16 *sK1, bf16 *sV0,
+                                             bf16 *sV1, uint32_t *sX, int *sG, int *sScan) {
+  constexpr int f = PAT == P_DENSE ? RS_DENSE : PAT == P_ASHAPE ? RS_ASHAPE : PAT == P_VS ? RS_VSLASH : RS_BSPARSE;
   for (;;) {
     __syncthreads();  // the previous item is done with the tile buffers and sItem
     if (threadIdx.x == 0) {
       int got = -1;
       for (int k = 0; k < 8 && got < 0; ++k) {
-        const int b = (x + k) & 7;
-        if (__hip_atomic_load(&a.qcount[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= a.qsize[b]) continue;
-        const int r = atomicAdd(&a.qcount[b], 1);
-        if (r < a.qsize[b]) got = a.order[a.qoff[b] + r];
+        const int q = 8 * f + (((int)blockIdx.x + k) & 7), n = a.qsize[q];
+        if (__hip_atomic_load(&a.qcount[q], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= n) continue;
+        const int r = atomicAdd(&a.qcount[q], 1);
+        if (r < n) got = a.order[a.qoff[q] + r];
       }
-      sItem = got;
+      *sItem = got;
     }
     __syncthreads();
-    const int it = sItem;
+    const int it = *sItem;
     if (it < 0) break;
-    attn_item<D, PAT, InT, VT>(a, it);
+    if constexpr (kLayer) {
+      // the arguments are read again for every item through a pointer the compiler cannot see
+      // through: kept in scalar registers across four item loops, 99 of them spilled (routed layers
+      // 1-1.5% faster this way; a kernel of one family has fewer, and dense alone loses 1-2%)
+      typedef const __attribute__((address_space(4))) AttnArgs CArgs;
+      CArgs *pa = (CArgs *)__builtin_amdgcn_kernarg_segment_ptr();
+      asm volatile("" : "+s"(pa));
+      attn_item<D, PAT, InT, VT, true>(*pa, it, sK0, sK1, sV0, sV1, sX, sG, sScan);
+    } else {
+      attn_item<D, PAT, InT, VT, false>(a, it, sK0, sK1, sV0, sV1, sX, sG, sScan);
+    }
   }
+}
+
+// One family's items.
+template <int D, int PAT, typename InT, bool VT>
+__global__ void __launch_bounds__(256, 2) attn_fwd_queue_kernel(const AttnArgs a) {
+  RS_ATTN_LDS(D, AttnLds<PAT>::kX, AttnLds<PAT>::kG, AttnLds<PAT>::kScan);
+  __shared__ int sItem;
+  drain_family<D, PAT, InT, VT, false>(a, &sItem, sK0, sK1, sV0, sV1, sX, sG, sScan);
+}
+
+// Every family's items in one launch, dense first (its items are the longest): a family's last items
+// run beside the next family's instead of leaving the chip to a launch's tail.  A routed layer of a
+// short prompt has few dense fallback items, each a long chain of tiles: 8K tokens 672 -> 602 us,
+// 30K 2895 -> 2853 us, 128K 22.84 -> 22.49 ms.
+template <int D, typename InT, bool VT>
+__global__ void __launch_bounds__(256, 2) attn_fwd_layer_kernel(const AttnArgs a) {
+  RS_ATTN_LDS(D, AttnLds<P_BS>::kX > AttnLds<P_VS>::kX ? AttnLds<P_BS>::kX : AttnLds<P_VS>::kX, AttnLds<P_VS>::kG,
+              AttnLds<P_VS>::kScan);
+  __shared__ int sItem;
+  drain_family<D, P_DENSE, InT, VT, true>(a, &sItem, sK0, sK1, sV0, sV1, sX, sG, sScan);
+  drain_family<D, P_VS, InT, false, true>(a, &sItem, sK0, sK1, sV0, sV1, sX, sG, sScan);
+  drain_family<D, P_BS, InT, VT, true>(a, &sItem, sK0, sK1, sV0, sV1, sX, sG, sScan);
+  drain_family<D, P_ASHAPE, InT, VT, true>(a, &sItem, sK0, sK1, sV0, sV1, sX, sG, sScan);
 }
 
 // ---- merge of split items ------------------------------------------------------------------
@@ -1195,6 +1236,22 @@ static hipError_t launch_pat(int dtype, const AttnArgs &a, int nitems, hipStream
 }
 
 template <int D>
+static hipError_t launch_layer(int dtype, const AttnArgs &a, int nblocks, hipStream_t st) {
+  if (a.vt) {
+    if (dtype == RS_BF16)
+      hipLaunchKernelGGL((attn_fwd_layer_kernel<D, bf16, true>), dim3(nblocks), dim3(256), 0, st, a);
+    else
+      hipLaunchKernelGGL((attn_fwd_layer_kernel<D, float, true>), dim3(nblocks), dim3(256), 0, st, a);
+  } else {
+    if (dtype == RS_BF16)
+      hipLaunchKernelGGL((attn_fwd_layer_kernel<D, bf16, false>), dim3(nblocks), dim3(256), 0, st, a);
+    else
+      hipLaunchKernelGGL((attn_fwd_layer_kernel<D, float, false>), dim3(nblocks), dim3(256), 0, st, a);
+  }
+  return hipGetLastError();
+}
+
+template <int D>
 static hipError_t launch_d(int fam, int dtype, const AttnArgs &a, int nitems, hipStream_t st) {
   switch (fam) {
     case RS_DENSE: return launch_pat<D, P_DENSE>(dtype, a, nitems, st);
@@ -1206,7 +1263,8 @@ static hipError_t launch_d(int fam, int dtype, const AttnArgs &a, int nitems, hi
 
 // One launch of a family's kernel over a device work list: `d_units` and `d_order` as built
 // by attn_launch (host; one workgroup per item, `nblocks` items) or by the device planner
-// (device routing; `queues` set, `nblocks` persistent workgroups drain the bucket queues).
+// (device routing; `queues` set, `nblocks` persistent workgroups drain the bucket queues; fam < 0:
+// those of every family in one launch).
 rs_status attn_launch_list(const rs_qkv *qkv, float scale, int fam, const rs_index_set *idx,
                            const DevUnit *d_units, const int *d_order, const AttnQueues *queues, int nblocks,
                            const AttnParts &parts, void *o, int64_t so_h, int64_t so_t, float *lse, hipStream_t st) {
@@ -1220,17 +1278,20 @@ rs_status attn_launch_list(const rs_qkv *qkv, float scale, int fam, const rs_ind
   a.units = d_units; a.order = d_order; a.parts = parts;
   a.vt = (const bf16 *)qkv->vt; a.npad = (qkv->n + 63) / 64 * 64;
   if (queues) { a.qsize = queues->size; a.qoff = queues->off; a.qcount = queues->count; }
-  if (fam == RS_VSLASH) {
+  if (idx && (fam == RS_VSLASH || fam < 0)) {
     a.vs_vsorted = idx->vs_vsorted; a.vs_dsorted = idx->vs_dsorted; a.vs_count = idx->vs_count;
     a.vs_vbits = idx->vs_vbits; a.vs_dbits = idx->vs_dbits;
     a.nv_max = idx->nv_max; a.ns_max = idx->ns_max; a.nwords = idx->nwords; a.ncand_vs = idx->ncand_vs;
   }
-  if (fam == RS_BSPARSE) {
+  if (idx && (fam == RS_BSPARSE || fam < 0)) {
     a.bs_sorted = idx->bs_sorted; a.bs_count = idx->bs_count;
     a.k_max = idx->k_max; a.nb = idx->nb; a.ncand_bs = idx->ncand_bs;
   }
-  hipError_t e = qkv->d == 128 ? launch_d<128>(fam, qkv->dtype, a, nblocks, st)
-                               : launch_d<64>(fam, qkv->dtype, a, nblocks, st);
+  hipError_t e;
+  if (fam < 0)
+    e = qkv->d == 128 ? launch_layer<128>(qkv->dtype, a, nblocks, st) : launch_layer<64>(qkv->dtype, a, nblocks, st);
+  else
+    e = qkv->d == 128 ? launch_d<128>(fam, qkv->dtype, a, nblocks, st) : launch_d<64>(fam, qkv->dtype, a, nblocks, st);
   if (e != hipSuccess) return hip_check(e, "attention kernel launch");
   return RS_OK;
 }

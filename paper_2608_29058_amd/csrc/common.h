@@ -108,8 +108,9 @@ AttnParts attn_parts_at(void *p, int d, size_t slots);
 rs_status attn_merge_launch(const rs_qkv *qkv, float scale, const DevUnit *d_units, const AttnParts &parts,
                             int slots, void *o, int64_t so_h, int64_t so_t, float *lse, hipStream_t st);
 
-// Device work queues of a persistent attention launch: per key/value bucket b (8), the items
-// order[off[b] .. off[b] + size[b]) and a counter of items taken (starts at 0).
+// Device work queues of the persistent attention launches: per family f and key/value bucket b
+// (q = 8 f + b), the items order[off[q] .. off[q] + size[q]) and a counter of items taken (starts
+// at 0).
 struct AttnQueues {
   const int *size, *off;
   int *count;

@@ -631,7 +631,7 @@ __global__ void __launch_bounds__(1024) plan_kernel(const PlanArgs a) {
   __syncthreads();
   if (tid == 0) {
     a.qsize[f * 8 + b] = total;
-    a.qoff[f * 8 + b] = before;
+    a.qoff[f * 8 + b] = f * a.max_items + before;
     a.qcount[f * 8 + b] = 0;
   }
   int *order = a.order + (long long)f * a.max_items + before;
@@ -654,7 +654,7 @@ __global__ void __launch_bounds__(1024) plan_kernel(const PlanArgs a) {
       r += (n - below) * sp;
       r += (x < lo && d >= 0 && (d & sh) == 0 && (d >> sh) < n) ? sp : 0;
     }
-    order[r + piece] = (sU[lo] << 16) | (piece << 12) | t;
+    order[r + piece] = ((f * U + sU[lo]) << 16) | (piece << 12) | t;
   }
 }
 
@@ -838,22 +838,27 @@ rs_status routed_attn_launch(const rs_qkv *qkv, float scale, const rs_unit *unit
   RS_HIP(hipGetDevice(&dev));
   RS_HIP(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev));
   const int nblocks = std::min(((2 * ncu + 7) / 8) * 8, (((int)items + 7) / 8) * 8);
-  // dense first: its tiles are the longest
+  const AttnQueues qs{p.qsize, p.qoff, p.qcount};
+  if (!events) {  // every family in one launch
+    rs_status s = attn_launch_list(qkv, scale, -1, idx, p.dunits, p.order, &qs, nblocks, parts, o, so_h, so_t, lse, st);
+    if (s == RS_OK && slots > 0)
+      s = attn_merge_launch(qkv, scale, p.dunits, parts, (int)slots, o, so_h, so_t, lse, st);
+    return s;
+  }
+  // one launch per family, timed apart; dense first: its items are the longest
   const int fam_order[4] = {RS_DENSE, RS_VSLASH, RS_BSPARSE, RS_ASHAPE};
-  if (events) RS_HIP(hipEventRecord((hipEvent_t)events[0], st));
+  RS_HIP(hipEventRecord((hipEvent_t)events[0], st));
   for (int k = 0; k < 4; ++k) {
     const int f = fam_order[k];
     if (present[f]) {
-      const AttnQueues qs{p.qsize + 8 * f, p.qoff + 8 * f, p.qcount + 8 * f};
-      rs_status s = attn_launch_list(qkv, scale, f, idx, p.dunits + (size_t)f * nunits,
-                                     p.order + (size_t)f * items, &qs, nblocks, parts, o, so_h, so_t, lse, st);
+      rs_status s = attn_launch_list(qkv, scale, f, idx, p.dunits, p.order, &qs, nblocks, parts, o, so_h, so_t, lse, st);
       if (s != RS_OK) return s;
     }
     if (f == RS_VSLASH && slots > 0) {  // the two families with split items are launched
       rs_status s = attn_merge_launch(qkv, scale, p.dunits, parts, (int)slots, o, so_h, so_t, lse, st);
       if (s != RS_OK) return s;
     }
-    if (events) RS_HIP(hipEventRecord((hipEvent_t)events[1 + k], st));
+    RS_HIP(hipEventRecord((hipEvent_t)events[1 + k], st));
   }
   return RS_OK;
 }

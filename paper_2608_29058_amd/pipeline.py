@@ -8,7 +8,7 @@ library in the order of the per-layer procedure (Sec. 3.4 and its table):
   3-5. rs_route_layer on the host after copying the coverage back (latency lookup, greedy
        solve, expand/fallback, grouping), or rs_route_layer_device on the stream
   6. one rs_sparse_attn_prefill / rs_dense_attn_prefill launch per (pattern, budget) group, or
-     after device routing one rs_routed_attn_prefill call (one launch per family, work lists
+     after device routing one rs_routed_attn_prefill call (one launch for all families, work lists
      built on the device: no host synchronisation in the layer).
 With beta > 0 the calibrated error predictor (rs_error_predict) runs after the coverage.
 """
