@@ -108,6 +108,13 @@ AttnParts attn_parts_at(void *p, int d, size_t slots);
 rs_status attn_merge_launch(const rs_qkv *qkv, float scale, const DevUnit *d_units, const AttnParts &parts,
                             int slots, void *o, int64_t so_h, int64_t so_t, float *lse, hipStream_t st);
 
+// fp32 Q, K and V rounded to bf16 in the workspace before the attention, as the kernels would on
+// load: rows the units read, [head][token][d].  bytes: 0 for bf16 inputs.
+size_t attn_cvt_bytes(const rs_qkv *qkv, const rs_unit *units, int32_t nunits);
+// Queues the conversion into `p` and describes the result in *out (qkv with bf16 arrays).
+rs_status attn_cvt_launch(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, void *p, rs_qkv *out,
+                          hipStream_t st);
+
 // Device work queues of the persistent attention launches: per family f and key/value bucket b
 // (q = 8 f + b), the items order[off[q] .. off[q] + size[q]) and a counter of items taken (starts
 // at 0).

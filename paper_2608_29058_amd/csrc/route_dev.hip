@@ -777,7 +777,8 @@ static void routed_counts(const rs_qkv *qkv, const rs_unit *units, int32_t nunit
 size_t routed_attn_ws_bytes(const rs_qkv *qkv, const rs_unit *units, int32_t nunits) {
   size_t items, slots;
   routed_counts(qkv, units, nunits, true, &items, &slots);
-  return routed_list_bytes(nunits, items) + attn_parts_bytes(qkv ? qkv->d : 0, slots);
+  return routed_list_bytes(nunits, items) + attn_parts_bytes(qkv ? qkv->d : 0, slots) +
+         attn_cvt_bytes(qkv, units, nunits);
 }
 
 rs_status routed_attn_launch(const rs_qkv *qkv, float scale, const rs_unit *units, int32_t nunits,
@@ -797,7 +798,17 @@ rs_status routed_attn_launch(const rs_qkv *qkv, float scale, const rs_unit *unit
   if (!ws || ws_bytes < need)
     return fail(RS_ERR_WORKSPACE, "routed attention workspace too small: need " + std::to_string(need) + " bytes");
   AttnParts parts{};
-  if (slots > 0) parts = attn_parts_at((char *)ws + need / 256 * 256, qkv->d, slots);
+  char *at = (char *)ws + need / 256 * 256;  // past the lists' end
+  if (slots > 0) parts = attn_parts_at(at, qkv->d, slots);
+  at += attn_parts_bytes(qkv->d, slots) / 256 * 256;
+  const size_t cvt = attn_cvt_bytes(qkv, units, nunits);
+  const rs_unit_table *tables = qkv->tables;
+  rs_qkv conv;
+  if (cvt > 0 && !((uintptr_t)ws & 15) && ws_bytes >= (size_t)(at - (char *)ws) + cvt) {
+    rs_status s = attn_cvt_launch(qkv, units, nunits, at, &conv, st);
+    if (s != RS_OK) return s;
+    qkv = &conv;
+  }
   Arena ar(ws, ws_bytes);
   rs_unit *d_units = ar.take<rs_unit>((size_t)nunits);
   int *d_q = ar.take<int>(3 * 32);
@@ -827,8 +838,8 @@ rs_status routed_attn_launch(const rs_qkv *qkv, float scale, const rs_unit *unit
   p.qcount = d_q + 64;
   // the unit list: from the caller's unit table, else copied into the workspace (from the
   // caller's array, which the copy reads before hipMemcpyAsync returns)
-  if (qkv->tables)
-    p.units = unit_tab_units(qkv->tables);
+  if (tables)
+    p.units = unit_tab_units(tables);
   else
     RS_HIP(hipMemcpyAsync(d_units, units, (size_t)nunits * sizeof(rs_unit), hipMemcpyHostToDevice, st));
   hipLaunchKernelGGL(plan_kernel, dim3(32), dim3(1024), 0, st, p);
