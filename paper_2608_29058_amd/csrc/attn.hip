@@ -66,6 +66,24 @@ struct AttnArgs {
   AttnParts parts;  // partial results of split items (dense and vertical-slash)
 };
 
+// A work list in kernel arguments: up to kDirectUnits units with the same rows and item height, sorted by
+// key/value bucket, whose items follow from the workgroup's index, so that the launch needs no
+// list in memory and no copy of one (4-5 us of the stream and the host's sorting before every
+// launch).  nu = 0: items and units come from the lists in AttnArgs.
+// Items are dealt to the non-empty buckets in turn, and a bucket that has run out drops out: position
+// x of the grid lies in the segment k with pos[k] <= x < pos[k + 1], where na[k] buckets (4-bit
+// numbers in act[k]) take turns from their item first[k] on.
+constexpr int kDirectUnits = 64;
+struct AttnDirect {
+  AttnArgs a;
+  int nu, tiles, nsplit, nseg;
+  int bstart[9];  // first unit of each bucket
+  int pos[9], first[8], na[8];
+  uint32_t act[8];
+  DevUnit u[kDirectUnits];
+};
+static_assert(sizeof(AttnDirect) <= 4096, "kernel arguments");
+
 constexpr int kMaxTiles = kMaxN / 64;  // key tiles of the longest supported sequence
 constexpr int kMaxGather = 2048;       // vertical columns gathered per query tile
 
@@ -130,12 +148,11 @@ struct AttnLds {
   __shared__ uint32_t sX[NX];                                                                   \
   __shared__ int sG[NG], sScan[NS]
 
-// One work item: piece `item >> 12 & 15` of query tile `item & 0xfff` of unit `item >> 16` of the
-// launch's unit list.
+// One work item: piece `item >> 12 & 15` of query tile `item & 0xfff` of unit U.
 // VT: V is read from the transposed copy (tiles of D rows x 64 keys), else from V itself.
 // sK0..sV1: the tile buffers; sX, sG, sScan: the pattern's LDS (AttnLds), all owned by the kernel.
 template <int D, int PAT, typename InT, bool VT, bool kLayer, typename Args>
-__device__ __forceinline__ void attn_item(const Args &a, const int item, bf16 *sK0, bf16 *sK1, bf16 *sV0,
+__device__ __forceinline__ void attn_item(const Args &a, const DevUnit U, const int item, bf16 *sK0, bf16 *sK1, bf16 *sV0,
                                           bf16 *sV1, uint32_t *sX, int *sG, int *sScan) {
   constexpr int NW = 4, NT = 256, BM = 128;
   constexpr int KS = D / 16;             // k-steps of the QK^T contraction
@@ -164,7 +181,6 @@ __device__ __forceinline__ void attn_item(const Args &a, const int item, bf16 *s
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, hh = lane >> 5;
 
-  const DevUnit U = a.units[item >> 16];
   const int qt = item & 0xfff;
   // pieces along the keys (dense and vertical-slash): this item takes the tiles of piece `piece`
   constexpr bool kSplit = PAT == P_DENSE || PAT == P_VS;
@@ -173,9 +189,8 @@ __device__ __forceinline__ void attn_item(const Args &a, const int item, bf16 *s
   // pieces of this item's `nt` tiles: a short list takes fewer, and the workgroups beyond them have
   // nothing to do (false)
   [[maybe_unused]] auto take_piece = [&](int nt) -> bool {
-    const int pt = a.units[item >> 16].ptiles;
-    npiece = min(npiece, max(1, (nt + pt - 1) / pt));
-    if (piece == 0 && threadIdx.x == 0) a.parts.n[a.units[item >> 16].pbase + qt * a.units[item >> 16].nsplit] = npiece;
+    npiece = min(npiece, max(1, (nt + U.ptiles - 1) / U.ptiles));
+    if (piece == 0 && threadIdx.x == 0) a.parts.n[U.pbase + qt * U.nsplit] = npiece;
     return piece < npiece;
   };
   const int head = U.head, s0 = U.s0, s1 = U.s1;
@@ -890,7 +905,7 @@ __device__ __forceinline__ void attn_item(const Args &a, const int item, bf16 *s
     if (__builtin_expect(npiece > 1, 0)) {
       // this piece's unnormalised O, running max and sum; attn_merge_kernel finishes the rows
       if (i < r_lo || i >= r_hi) return;
-      const int slot0 = a.units[item >> 16].pbase + qt * a.units[item >> 16].nsplit;
+      const int slot0 = U.pbase + qt * U.nsplit;
       const long long at = (long long)(slot0 + piece) * BM + (i - base);
       float *po = a.parts.o + at * D;
 #pragma unroll
@@ -923,11 +938,36 @@ __device__ __forceinline__ void attn_item(const Args &a, const int item, bf16 *s
     a.lse[(long long)whead * a.n + i] = l_tot > 0.f ? m_run * a.scale + logf(l_tot) : -INFINITY;
 }
 
-// attn_fwd_kernel: workgroup b runs item order[b].
+// attn_fwd_kernel: one item per workgroup, from the kernel arguments or the list in memory.
 template <int D, int PAT, typename InT, bool VT>
-__global__ void __launch_bounds__(256, 2) attn_fwd_kernel(const AttnArgs a) {
+__global__ void __launch_bounds__(256, 2) attn_fwd_kernel(const AttnDirect p) {
   RS_ATTN_LDS(D, AttnLds<PAT>::kX, AttnLds<PAT>::kG, AttnLds<PAT>::kScan);
-  attn_item<D, PAT, InT, VT, false>(a, a.order[blockIdx.x], sK0, sK1, sV0, sV1, sX, sG, sScan);
+  int item;
+  DevUnit U;
+  if (p.nu > 0) {
+    const int x = (int)blockIdx.x;
+    int k = 0;
+    while (k + 1 < p.nseg && x >= p.pos[k + 1]) ++k;
+    const int rem = x - p.pos[k], turn = rem / p.na[k], j = rem - turn * p.na[k];
+    const int b = __builtin_amdgcn_readfirstlane((int)(p.act[k] >> (4 * j)) & 7);
+    const int i = p.first[k] + turn;  // item i of bucket b
+    // longest query tiles first, then the bucket's units, then the pieces of an item
+    const int u0 = p.bstart[b], per = (p.bstart[b + 1] - u0) * p.nsplit;
+    const int q = i / per, r = i - q * per, u = r / p.nsplit;
+    item = ((r - u * p.nsplit) << 12) | (p.tiles - 1 - q);
+    U = p.u[__builtin_amdgcn_readfirstlane(u0 + u)];
+  } else {
+    item = p.a.order[blockIdx.x];
+    U = p.a.units[item >> 16];
+  }
+  // (the merge of the two sources counts as varying over the lanes: back to scalar registers)
+  item = __builtin_amdgcn_readfirstlane(item);
+  int w[sizeof(DevUnit) / 4];
+  __builtin_memcpy(w, &U, sizeof(U));
+#pragma unroll
+  for (size_t k = 0; k < sizeof(DevUnit) / 4; ++k) w[k] = __builtin_amdgcn_readfirstlane(w[k]);
+  __builtin_memcpy(&U, w, sizeof(U));
+  attn_item<D, PAT, InT, VT, false>(p.a, U, item, sK0, sK1, sV0, sV1, sX, sG, sScan);
 }
 
 // The persistent kernels take items from queues: family f's queue of key/value bucket b holds the
@@ -961,9 +1001,9 @@ __device__ __forceinline__ void drain_family(const AttnArgs &a, int *sItem, bf16
       typedef const __attribute__((address_space(4))) AttnArgs CArgs;
       CArgs *pa = (CArgs *)__builtin_amdgcn_kernarg_segment_ptr();
       asm volatile("" : "+s"(pa));
-      attn_item<D, PAT, InT, VT, true>(*pa, it, sK0, sK1, sV0, sV1, sX, sG, sScan);
+      attn_item<D, PAT, InT, VT, true>(*pa, pa->units[it >> 16], it, sK0, sK1, sV0, sV1, sX, sG, sScan);
     } else {
-      attn_item<D, PAT, InT, VT, false>(a, it, sK0, sK1, sV0, sV1, sX, sG, sScan);
+      attn_item<D, PAT, InT, VT, false>(a, a.units[it >> 16], it, sK0, sK1, sV0, sV1, sX, sG, sScan);
     }
   }
 }
@@ -1070,23 +1110,43 @@ rs_status attn_cvt_launch(const rs_qkv *qkv, const rs_unit *units, int32_t nunit
 }
 
 // ---- merge of split items ------------------------------------------------------------------
-// grid (slots, 8), 256 threads: 16 rows of an item per workgroup, 16 threads per row.  Piece p of
+// grid (slots, or items with a list in the arguments; 8), 256 threads: 16 rows of an item per
+// workgroup, 16 threads per row.  Piece p of
 // a row holds O_p relative to its own running max m_p: with M the largest and w_p = exp(m_p - M),
 // O = sum w_p O_p / sum w_p l_p, in piece order (a fixed order: the result is deterministic).  A
 // piece that kept no key of the row has l_p = 0 and m_p = -inf.  Bound by reading the pieces.
+// Its units in kernel arguments, as AttnDirect holds them (tiles = 0: units and items in memory).
+struct MergeDirect {
+  int tiles, nsplit, s0, s1;
+  int head[kDirectUnits];
+};
 template <int D>
-__global__ void __launch_bounds__(256) attn_merge_kernel(const DevUnit *units, const AttnParts parts, bf16 *o,
-                                                         long long so_h, long long so_t, float *lse, int n, float c,
-                                                         float scale) {
+__global__ void __launch_bounds__(256) attn_merge_kernel(const DevUnit *units, const AttnParts parts,
+                                                         const MergeDirect m, bf16 *o, long long so_h, long long so_t,
+                                                         float *lse, int n, float c, float scale) {
   constexpr int EPT = D / 16, BM = 128;  // elements per thread, rows of an item
-  const int slot0 = blockIdx.x, item = parts.items[slot0];
-  if (item < 0) return;
+  int slot0 = blockIdx.x, qt, head, s0, s1;
+  if (m.tiles > 0) {
+    const int u = slot0 / m.tiles;
+    qt = slot0 - u * m.tiles;
+    slot0 *= m.nsplit;
+    head = m.head[u];
+    s0 = m.s0;
+    s1 = m.s1;
+  } else {
+    const int item = parts.items[slot0];
+    if (item < 0) return;
+    const DevUnit U = units[item >> 16];
+    qt = item & 0xfff;
+    head = U.head;
+    s0 = U.s0;
+    s1 = U.s1;
+  }
   const int np = parts.n[slot0];
   if (np <= 1) return;  // the item's one workgroup wrote the rows itself
-  const DevUnit U = units[item >> 16];
-  const int base = (U.s0 / BM + (item & 0xfff)) * BM;
+  const int base = (s0 / BM + qt) * BM;
   const int r = blockIdx.y * 16 + (threadIdx.x >> 4), i = base + r, x = threadIdx.x & 15;
-  if (i < U.s0 || i >= U.s1) return;
+  if (i < s0 || i >= s1) return;
   const float *ml = parts.ml + ((long long)slot0 * BM + r) * 2;
   float M = -INFINITY;
   for (int p = 0; p < np; ++p) M = fmaxf(M, ml[(long long)p * BM * 2]);
@@ -1106,11 +1166,11 @@ __global__ void __launch_bounds__(256) attn_merge_kernel(const DevUnit *units, c
     }
   }
   const float inv = L > 0.f ? 1.f / L : 0.f;
-  bf16 *op = o + (long long)U.head * so_h + (long long)i * so_t + EPT * x;
+  bf16 *op = o + (long long)head * so_h + (long long)i * so_t + EPT * x;
 #pragma unroll
   for (int e = 0; e < EPT; e += 4)
     *(u32x2 *)(op + e) = u32x2{pack_bf16x2(acc[e] * inv, acc[e + 1] * inv), pack_bf16x2(acc[e + 2] * inv, acc[e + 3] * inv)};
-  if (lse && x == 0) lse[(long long)U.head * n + i] = L > 0.f ? M * scale + logf(L) : -INFINITY;
+  if (lse && x == 0) lse[(long long)head * n + i] = L > 0.f ? M * scale + logf(L) : -INFINITY;
 }
 
 size_t attn_parts_bytes(int d, size_t slots) {
@@ -1133,17 +1193,23 @@ AttnParts attn_parts_at(void *p, int d, size_t slots) {
   return a;
 }
 
-rs_status attn_merge_launch(const rs_qkv *qkv, float scale, const DevUnit *d_units, const AttnParts &parts,
-                            int slots, void *o, int64_t so_h, int64_t so_t, float *lse, hipStream_t st) {
-  const dim3 grid(slots, 8);
+static rs_status merge_launch(const rs_qkv *qkv, float scale, const DevUnit *d_units, const AttnParts &parts,
+                              const MergeDirect &m, int blocks, void *o, int64_t so_h, int64_t so_t, float *lse,
+                              hipStream_t st) {
+  const dim3 grid(blocks, 8);
   if (qkv->d == 128)
-    hipLaunchKernelGGL(attn_merge_kernel<128>, grid, dim3(256), 0, st, d_units, parts, (bf16 *)o, (long long)so_h,
+    hipLaunchKernelGGL(attn_merge_kernel<128>, grid, dim3(256), 0, st, d_units, parts, m, (bf16 *)o, (long long)so_h,
                        (long long)so_t, lse, qkv->n, scale * kLog2e, scale);
   else
-    hipLaunchKernelGGL(attn_merge_kernel<64>, grid, dim3(256), 0, st, d_units, parts, (bf16 *)o, (long long)so_h,
+    hipLaunchKernelGGL(attn_merge_kernel<64>, grid, dim3(256), 0, st, d_units, parts, m, (bf16 *)o, (long long)so_h,
                        (long long)so_t, lse, qkv->n, scale * kLog2e, scale);
   RS_HIP(hipGetLastError());
   return RS_OK;
+}
+
+rs_status attn_merge_launch(const rs_qkv *qkv, float scale, const DevUnit *d_units, const AttnParts &parts,
+                            int slots, void *o, int64_t so_h, int64_t so_t, float *lse, hipStream_t st) {
+  return merge_launch(qkv, scale, d_units, parts, MergeDirect{}, slots, o, so_h, so_t, lse, st);
 }
 
 // ---- V^T: [hkv][d][npad] bf16, keys permuted within groups of 16 ---------------------------
@@ -1282,35 +1348,25 @@ static void build_order(const rs_unit *units, int nunits, int group, int bm, con
       if (i < buckets[b].size()) order.push_back(buckets[b][i].second);
 }
 
+template <int D, int PAT, typename InT, bool VT>
+static void launch_one(const AttnDirect &p, int nblocks, hipStream_t st) {
+  if (p.a.qsize)
+    hipLaunchKernelGGL((attn_fwd_queue_kernel<D, PAT, InT, VT>), dim3(nblocks), dim3(256), 0, st, p.a);
+  else
+    hipLaunchKernelGGL((attn_fwd_kernel<D, PAT, InT, VT>), dim3(nblocks), dim3(256), 0, st, p);
+}
+
 template <int D, int PAT>
-static hipError_t launch_pat(int dtype, const AttnArgs &a, int nitems, hipStream_t st) {
-  if (a.vt) {
-    if constexpr (PAT != P_VS) {  // vertical-slash gathers V rows: it keeps the row-major V
-      if (a.qsize) {
-        if (dtype == RS_BF16)
-          hipLaunchKernelGGL((attn_fwd_queue_kernel<D, PAT, bf16, true>), dim3(nitems), dim3(256), 0, st, a);
-        else
-          hipLaunchKernelGGL((attn_fwd_queue_kernel<D, PAT, float, true>), dim3(nitems), dim3(256), 0, st, a);
-      } else {
-        if (dtype == RS_BF16)
-          hipLaunchKernelGGL((attn_fwd_kernel<D, PAT, bf16, true>), dim3(nitems), dim3(256), 0, st, a);
-        else
-          hipLaunchKernelGGL((attn_fwd_kernel<D, PAT, float, true>), dim3(nitems), dim3(256), 0, st, a);
-      }
+static hipError_t launch_pat(int dtype, const AttnDirect &p, int nblocks, hipStream_t st) {
+  if constexpr (PAT != P_VS) {  // vertical-slash gathers V rows: it keeps the row-major V
+    if (p.a.vt) {
+      if (dtype == RS_BF16) launch_one<D, PAT, bf16, true>(p, nblocks, st);
+      else launch_one<D, PAT, float, true>(p, nblocks, st);
       return hipGetLastError();
     }
   }
-  if (a.qsize) {
-    if (dtype == RS_BF16)
-      hipLaunchKernelGGL((attn_fwd_queue_kernel<D, PAT, bf16, false>), dim3(nitems), dim3(256), 0, st, a);
-    else
-      hipLaunchKernelGGL((attn_fwd_queue_kernel<D, PAT, float, false>), dim3(nitems), dim3(256), 0, st, a);
-  } else {
-    if (dtype == RS_BF16)
-      hipLaunchKernelGGL((attn_fwd_kernel<D, PAT, bf16, false>), dim3(nitems), dim3(256), 0, st, a);
-    else
-      hipLaunchKernelGGL((attn_fwd_kernel<D, PAT, float, false>), dim3(nitems), dim3(256), 0, st, a);
-  }
+  if (dtype == RS_BF16) launch_one<D, PAT, bf16, false>(p, nblocks, st);
+  else launch_one<D, PAT, float, false>(p, nblocks, st);
   return hipGetLastError();
 }
 
@@ -1331,32 +1387,25 @@ static hipError_t launch_layer(int dtype, const AttnArgs &a, int nblocks, hipStr
 }
 
 template <int D>
-static hipError_t launch_d(int fam, int dtype, const AttnArgs &a, int nitems, hipStream_t st) {
+static hipError_t launch_d(int fam, int dtype, const AttnDirect &p, int nblocks, hipStream_t st) {
   switch (fam) {
-    case RS_DENSE: return launch_pat<D, P_DENSE>(dtype, a, nitems, st);
-    case RS_ASHAPE: return launch_pat<D, P_ASHAPE>(dtype, a, nitems, st);
-    case RS_VSLASH: return launch_pat<D, P_VS>(dtype, a, nitems, st);
-    default: return launch_pat<D, P_BS>(dtype, a, nitems, st);
+    case RS_DENSE: return launch_pat<D, P_DENSE>(dtype, p, nblocks, st);
+    case RS_ASHAPE: return launch_pat<D, P_ASHAPE>(dtype, p, nblocks, st);
+    case RS_VSLASH: return launch_pat<D, P_VS>(dtype, p, nblocks, st);
+    default: return launch_pat<D, P_BS>(dtype, p, nblocks, st);
   }
 }
 
-// One launch of a family's kernel over a device work list: `d_units` and `d_order` as built
-// by attn_launch (host; one workgroup per item, `nblocks` items) or by the device planner
-// (device routing; `queues` set, `nblocks` persistent workgroups drain the bucket queues; fam < 0:
-// those of every family in one launch).
-rs_status attn_launch_list(const rs_qkv *qkv, float scale, int fam, const rs_index_set *idx,
-                           const DevUnit *d_units, const int *d_order, const AttnQueues *queues, int nblocks,
-                           const AttnParts &parts, void *o, int64_t so_h, int64_t so_t, float *lse, hipStream_t st) {
-  if (nblocks <= 0) return RS_OK;
+static AttnArgs attn_args(const rs_qkv *qkv, float scale, int fam, const rs_index_set *idx, const AttnParts &parts,
+                          void *o, int64_t so_h, int64_t so_t, float *lse) {
   AttnArgs a{};
   a.q = qkv->q; a.k = qkv->k; a.v = qkv->v;
   a.sq_h = qkv->sq_h; a.sq_t = qkv->sq_t; a.sk_h = qkv->sk_h; a.sk_t = qkv->sk_t;
   a.sv_h = qkv->sv_h; a.sv_t = qkv->sv_t;
   a.o = (bf16 *)o; a.so_h = so_h; a.so_t = so_t; a.lse = lse;
   a.n = qkv->n; a.group = qkv->hq / qkv->hkv; a.scale = scale; a.c = scale * kLog2e;
-  a.units = d_units; a.order = d_order; a.parts = parts;
+  a.parts = parts;
   a.vt = (const bf16 *)qkv->vt; a.npad = (qkv->n + 63) / 64 * 64;
-  if (queues) { a.qsize = queues->size; a.qoff = queues->off; a.qcount = queues->count; }
   if (idx && (fam == RS_VSLASH || fam < 0)) {
     a.vs_vsorted = idx->vs_vsorted; a.vs_dsorted = idx->vs_dsorted; a.vs_count = idx->vs_count;
     a.vs_vbits = idx->vs_vbits; a.vs_dbits = idx->vs_dbits;
@@ -1366,13 +1415,77 @@ rs_status attn_launch_list(const rs_qkv *qkv, float scale, int fam, const rs_ind
     a.bs_sorted = idx->bs_sorted; a.bs_count = idx->bs_count;
     a.k_max = idx->k_max; a.nb = idx->nb; a.ncand_bs = idx->ncand_bs;
   }
+  return a;
+}
+
+// The persistent launch of a family (fam < 0: of every family) over the device planner's queues:
+// `nblocks` workgroups drain them.
+rs_status attn_launch_queues(const rs_qkv *qkv, float scale, int fam, const rs_index_set *idx,
+                             const DevUnit *d_units, const int *d_order, const AttnQueues &queues, int nblocks,
+                             const AttnParts &parts, void *o, int64_t so_h, int64_t so_t, float *lse, hipStream_t st) {
+  if (nblocks <= 0) return RS_OK;
+  AttnDirect p{};
+  p.a = attn_args(qkv, scale, fam, idx, parts, o, so_h, so_t, lse);
+  p.a.units = d_units; p.a.order = d_order;
+  p.a.qsize = queues.size; p.a.qoff = queues.off; p.a.qcount = queues.count;
   hipError_t e;
   if (fam < 0)
-    e = qkv->d == 128 ? launch_layer<128>(qkv->dtype, a, nblocks, st) : launch_layer<64>(qkv->dtype, a, nblocks, st);
+    e = qkv->d == 128 ? launch_layer<128>(qkv->dtype, p.a, nblocks, st) : launch_layer<64>(qkv->dtype, p.a, nblocks, st);
   else
-    e = qkv->d == 128 ? launch_d<128>(fam, qkv->dtype, a, nblocks, st) : launch_d<64>(fam, qkv->dtype, a, nblocks, st);
+    e = qkv->d == 128 ? launch_d<128>(fam, qkv->dtype, p, nblocks, st) : launch_d<64>(fam, qkv->dtype, p, nblocks, st);
   if (e != hipSuccess) return hip_check(e, "attention kernel launch");
   return RS_OK;
+}
+
+// Fills p's list of units for units of the same rows that all have mates or all have none
+// (taken-along ones apart); false when the list does not fit.  `mate` as pair_units gives it.
+static bool direct_list(const rs_unit *units, int nunits, int group, const std::vector<int> &mate,
+                        const std::vector<DevUnit> &du, AttnDirect &p) {
+  int cnt[8] = {0, 0, 0, 0, 0, 0, 0, 0}, nu = 0, lead = -1;
+  for (int u = 0; u < nunits; ++u) {
+    if (mate[u] == -2) continue;
+    if (lead < 0) lead = u;
+    if (units[u].s0 != units[lead].s0 || units[u].s1 != units[lead].s1 || (mate[u] >= 0) != (mate[lead] >= 0) ||
+        ++nu > kDirectUnits)
+      return false;
+    ++cnt[(units[u].head / group) & 7];
+  }
+  if (lead < 0) return false;
+  p.nu = nu;
+  p.tiles = tiles_of(units[lead], mate[lead] >= 0 ? 64 : 128);
+  p.nsplit = du[lead].nsplit;
+  int fill[8];
+  for (int b = 0; b < 8; ++b) {
+    fill[b] = p.bstart[b];
+    p.bstart[b + 1] = p.bstart[b] + cnt[b];
+  }
+  for (int u = 0; u < nunits; ++u)
+    if (mate[u] != -2) {
+      const int at = fill[(units[u].head / group) & 7]++;
+      p.u[at] = du[u];
+      p.u[at].pbase = at * p.tiles * p.nsplit;
+    }
+  // segments of the grid: buckets in turn until the shortest of those left runs out
+  const int per = p.tiles * p.nsplit;  // items per unit
+  int done = 0, pos = 0;
+  for (;;) {
+    int na = 0, mn = 0;
+    uint32_t act = 0;
+    for (int b = 0; b < 8; ++b)
+      if (cnt[b] * per > done) {
+        act |= (uint32_t)b << (4 * na++);
+        mn = mn == 0 ? cnt[b] * per : std::min(mn, cnt[b] * per);
+      }
+    if (na == 0) break;
+    p.pos[p.nseg] = pos;
+    p.first[p.nseg] = done;
+    p.na[p.nseg] = na;
+    p.act[p.nseg++] = act;
+    pos += (mn - done) * na;
+    done = mn;
+  }
+  p.pos[p.nseg] = pos;
+  return true;
 }
 
 // Shared entry of the dense and sparse calls (arguments validated by the caller).
@@ -1387,18 +1500,21 @@ rs_status attn_launch(const rs_qkv *qkv, float scale, const rs_unit *units, int3
   if (fam == RS_BSPARSE) pair_units(units, nunits, group, mate);
   // items split along the keys, where the workspace holds their partial results too
   std::vector<SplitRule> split(nunits, SplitRule{1, 1});
-  size_t slots = 0;
+  size_t slots = 0, items = 0;
   for (int u = 0; u < nunits; ++u) {
+    if (mate[u] == -2) continue;
     split[u] = attn_split(qkv->hq, qkv->d, units[u].s0, units[u].s1, fam);
-    if (split[u].nsplit > 1) slots += (size_t)tiles_of(units[u], bm) * split[u].nsplit;
+    const size_t nt = (size_t)tiles_of(units[u], mate[u] >= 0 ? 64 : bm);
+    if (split[u].nsplit > 1) slots += nt * split[u].nsplit;
+    items += nt * split[u].nsplit;
   }
-  build_order(units, nunits, group, bm, mate, split, order);
-  size_t lbytes = attn_list_bytes(nunits, order.size());
+  size_t lbytes = attn_list_bytes(nunits, items);
   if (slots > 0 && (!ws || ((uintptr_t)ws & 15) || ws_bytes < lbytes + attn_parts_bytes(qkv->d, slots))) {
+    for (int u = 0; u < nunits; ++u)
+      if (split[u].nsplit > 1) items -= (size_t)tiles_of(units[u], bm) * (split[u].nsplit - 1);
     slots = 0;
     std::fill(split.begin(), split.end(), SplitRule{1, 1});
-    build_order(units, nunits, group, bm, mate, split, order);
-    lbytes = attn_list_bytes(nunits, order.size());
+    lbytes = attn_list_bytes(nunits, items);
   }
   if (!ws || ws_bytes < lbytes)
     return fail(RS_ERR_WORKSPACE, "attention workspace too small: need " + std::to_string(lbytes) +
@@ -1414,33 +1530,50 @@ rs_status attn_launch(const rs_qkv *qkv, float scale, const rs_unit *units, int3
     if (rc != RS_OK) return rc;
     qkv = &conv;
   }
-  // host staging: [DevUnit x nunits][order], and the split items by partial slot
-  Arena ar(ws, ws_bytes);
-  DevUnit *d_units = ar.take<DevUnit>((size_t)nunits);
-  int *d_order = ar.take<int>(order.size());
-  const size_t off_order = (char *)d_order - (char *)ws;
-  std::vector<char> stage(off_order + order.size() * sizeof(int));
-  std::vector<int> items(slots, -1);
-  DevUnit *h_units = (DevUnit *)stage.data();
+  std::vector<DevUnit> du(nunits);
   int pbase = 0;
   for (int u = 0; u < nunits; ++u) {
-    const int ns = split[u].nsplit;
-    h_units[u] = DevUnit{units[u].head, units[u].s0, units[u].s1, cand_local, units[u].slot,
-                         fam == RS_ASHAPE ? cand->a : 0, fam == RS_ASHAPE ? cand->b : 0,
-                         mate[u] >= 0 ? units[mate[u]].head + 1 : 0, cand_local, ns, split[u].ptiles, pbase};
-    if (ns > 1)
-      for (int t = 0; t < tiles_of(units[u], bm); ++t, pbase += ns) items[pbase] = (u << 16) | t;
+    du[u] = DevUnit{units[u].head, units[u].s0, units[u].s1, cand_local, units[u].slot,
+                    fam == RS_ASHAPE ? cand->a : 0, fam == RS_ASHAPE ? cand->b : 0,
+                    mate[u] >= 0 ? units[mate[u]].head + 1 : 0, cand_local, split[u].nsplit, split[u].ptiles, pbase};
+    if (split[u].nsplit > 1) pbase += tiles_of(units[u], bm) * split[u].nsplit;
   }
-  memcpy(stage.data() + off_order, order.data(), order.size() * sizeof(int));
-  RS_HIP(hipMemcpyAsync(ws, stage.data(), stage.size(), hipMemcpyHostToDevice, st));
+  AttnDirect p{};
+  p.a = attn_args(qkv, scale, fam, idx, parts, o, so_h, so_t, lse);
+  MergeDirect md{};
+  DevUnit *d_units = nullptr;
+  if (direct_list(units, nunits, group, mate, du, p)) {
+    md = MergeDirect{p.tiles, p.nsplit, p.u[0].s0, p.u[0].s1, {}};
+    for (int u = 0; u < p.nu; ++u) md.head[u] = p.u[u].head;
+  } else {
+    // the list in the workspace: [DevUnit x nunits][order], and the split items by partial slot
+    p.nu = 0;
+    build_order(units, nunits, group, bm, mate, split, order);
+    Arena ar(ws, ws_bytes);
+    d_units = ar.take<DevUnit>((size_t)nunits);
+    int *d_order = ar.take<int>(order.size());
+    const size_t off_order = (char *)d_order - (char *)ws;
+    std::vector<char> stage(off_order + order.size() * sizeof(int));
+    memcpy(stage.data(), du.data(), du.size() * sizeof(DevUnit));
+    memcpy(stage.data() + off_order, order.data(), order.size() * sizeof(int));
+    RS_HIP(hipMemcpyAsync(ws, stage.data(), stage.size(), hipMemcpyHostToDevice, st));
+    if (slots > 0) {
+      std::vector<int> h_items(slots, -1);
+      for (int u = 0; u < nunits; ++u)
+        if (split[u].nsplit > 1)
+          for (int t = 0; t < tiles_of(units[u], bm); ++t) h_items[du[u].pbase + t * split[u].nsplit] = (u << 16) | t;
+      RS_HIP(hipMemcpyAsync(parts.items, h_items.data(), h_items.size() * sizeof(int), hipMemcpyHostToDevice, st));
+    }
+    p.a.units = d_units;
+    p.a.order = d_order;
+  }
+  const hipError_t e = qkv->d == 128 ? launch_d<128>(fam, qkv->dtype, p, (int)items, st)
+                                     : launch_d<64>(fam, qkv->dtype, p, (int)items, st);
+  if (e != hipSuccess) return hip_check(e, "attention kernel launch");
   if (slots > 0)
-    RS_HIP(hipMemcpyAsync(parts.items, items.data(), items.size() * sizeof(int), hipMemcpyHostToDevice, st));
-
-  rs_status rc = attn_launch_list(qkv, scale, fam, idx, d_units, d_order, nullptr, (int)order.size(), parts, o, so_h,
-                                  so_t, lse, st);
-  if (rc == RS_OK && slots > 0)
-    rc = attn_merge_launch(qkv, scale, d_units, parts, (int)slots, o, so_h, so_t, lse, st);
-  return rc;
+    return merge_launch(qkv, scale, d_units, parts, md, md.tiles > 0 ? p.nu * p.tiles : (int)slots, o, so_h, so_t, lse,
+                        st);
+  return RS_OK;
 }
 
 }  // namespace rs

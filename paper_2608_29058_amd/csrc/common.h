@@ -123,10 +123,10 @@ struct AttnQueues {
   int *count;
 };
 
-// One launch of a family's attention kernel over a device work list (attn.hip).
-rs_status attn_launch_list(const rs_qkv *qkv, float scale, int fam, const rs_index_set *idx,
-                           const DevUnit *d_units, const int *d_order, const AttnQueues *queues, int nblocks,
-                           const AttnParts &parts, void *o, int64_t so_h, int64_t so_t, float *lse, hipStream_t st);
+// The persistent launch of a family (fam < 0: of every family) over the planner's queues (attn.hip).
+rs_status attn_launch_queues(const rs_qkv *qkv, float scale, int fam, const rs_index_set *idx,
+                             const DevUnit *d_units, const int *d_order, const AttnQueues &queues, int nblocks,
+                             const AttnParts &parts, void *o, int64_t so_h, int64_t so_t, float *lse, hipStream_t st);
 
 // bump allocator over a caller workspace
 struct Arena {

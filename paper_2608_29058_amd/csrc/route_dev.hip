@@ -851,7 +851,7 @@ rs_status routed_attn_launch(const rs_qkv *qkv, float scale, const rs_unit *unit
   const int nblocks = std::min(((2 * ncu + 7) / 8) * 8, (((int)items + 7) / 8) * 8);
   const AttnQueues qs{p.qsize, p.qoff, p.qcount};
   if (!events) {  // every family in one launch
-    rs_status s = attn_launch_list(qkv, scale, -1, idx, p.dunits, p.order, &qs, nblocks, parts, o, so_h, so_t, lse, st);
+    rs_status s = attn_launch_queues(qkv, scale, -1, idx, p.dunits, p.order, qs, nblocks, parts, o, so_h, so_t, lse, st);
     if (s == RS_OK && slots > 0)
       s = attn_merge_launch(qkv, scale, p.dunits, parts, (int)slots, o, so_h, so_t, lse, st);
     return s;
@@ -862,7 +862,7 @@ rs_status routed_attn_launch(const rs_qkv *qkv, float scale, const rs_unit *unit
   for (int k = 0; k < 4; ++k) {
     const int f = fam_order[k];
     if (present[f]) {
-      rs_status s = attn_launch_list(qkv, scale, f, idx, p.dunits, p.order, &qs, nblocks, parts, o, so_h, so_t, lse, st);
+      rs_status s = attn_launch_queues(qkv, scale, f, idx, p.dunits, p.order, qs, nblocks, parts, o, so_h, so_t, lse, st);
       if (s != RS_OK) return s;
     }
     if (f == RS_VSLASH && slots > 0) {  // the two families with split items are launched
