@@ -19,6 +19,7 @@
 namespace rs {
 
 constexpr int kMaxCandFam = 8;
+constexpr int kArgUnits = 512;  // units whose key lengths travel in kernel arguments
 
 // The helpers below run over a group of NT threads: the whole workgroup, or with NT = 64 one
 // wave of it (each wave then works on its own data and LDS, synchronising only itself).
@@ -233,13 +234,15 @@ __device__ int bits_to_list(const uint32_t *bits, int nwords, int *out, int cap,
 struct VsArgs {
   const float *col, *diag;
   int n, nunits, ncand_vs;
-  const int *s1;  // [nunits]
+  const int *s1;  // [nunits], or NULL: s1_arg
   int nv[kMaxCandFam], ns[kMaxCandFam];
   int nv_max, ns_max, nwords;
   int gcap;  // capacity of the LDS gather of the largest set
   int *vsorted, *dsorted, *count;
   uint32_t *vbits, *dbits;
+  int s1_arg[kArgUnits];  // key lengths of a short unit list (no copy to the device)
 };
+static_assert(sizeof(VsArgs) <= 4096, "kernel arguments");
 
 // grid: (2, nunits); blockIdx.x = array (0: V from col, 1: D from diag).  Budgets of the family
 // are nested prefixes of one ranking: a superset of the largest set is taken from the whole
@@ -260,7 +263,7 @@ __global__ void __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(8, 8)
   __shared__ int sHist[256 * (NT / 64)], sBcast[3], sWave[NT / 64];
   const int arr = blockIdx.x;
   const int u = blockIdx.y;
-  const int s1 = a.s1[u];
+  const int s1 = a.s1 ? a.s1[u] : a.s1_arg[u];
   // the array and its offset: D selects diagonals [1, s1) and forces diagonal 0
   const float *vals = arr == 0 ? a.col + (long long)u * a.n : a.diag + (long long)u * a.n + 1;
   const int len = arr == 0 ? s1 : s1 - 1, off = arr == 0 ? 0 : 1;
@@ -527,7 +530,7 @@ rs_status build_indices_launch(const rs_probe_out *sc, const rs_unit *units, int
     }
   }
   if (nvs > 0) {
-    // unit key lengths: from the probe's unit table, else uploaded into the workspace
+    // unit key lengths: from the probe's unit table, else in the arguments or the workspace
     const int *d_s1 = nullptr;
     if (sc->tables) {
       d_s1 = unit_tab_s1(sc->tables);
@@ -535,11 +538,15 @@ rs_status build_indices_launch(const rs_probe_out *sc, const rs_unit *units, int
       Arena ar(ws, ws_bytes);
       int *w_s1 = ar.take<int>(nunits);
       if (!ws || !ar.ok()) return fail(RS_ERR_WORKSPACE, "index workspace too small");
-      std::vector<int> hs1(nunits);
-      for (int u = 0; u < nunits; ++u) hs1[u] = units[u].s1;
-      // the pageable host vector is copied before hipMemcpyAsync returns
-      RS_HIP(hipMemcpyAsync(w_s1, hs1.data(), nunits * sizeof(int), hipMemcpyHostToDevice, st));
-      d_s1 = w_s1;
+      if (nunits <= kArgUnits) {
+        for (int u = 0; u < nunits; ++u) va.s1_arg[u] = units[u].s1;
+      } else {
+        std::vector<int> hs1(nunits);
+        for (int u = 0; u < nunits; ++u) hs1[u] = units[u].s1;
+        // the pageable host vector is copied before hipMemcpyAsync returns
+        RS_HIP(hipMemcpyAsync(w_s1, hs1.data(), nunits * sizeof(int), hipMemcpyHostToDevice, st));
+        d_s1 = w_s1;
+      }
     }
     va.col = sc->col; va.diag = sc->diag; va.n = sc->n; va.nunits = nunits; va.ncand_vs = nvs;
     va.s1 = d_s1; va.nv_max = out->nv_max; va.ns_max = out->ns_max; va.nwords = out->nwords;
