@@ -74,6 +74,20 @@ struct AttnArgs {
 // x of the grid lies in the segment k with pos[k] <= x < pos[k + 1], where na[k] buckets (4-bit
 // numbers in act[k]) take turns from their item first[k] on.
 constexpr int kDirectUnits = 64;
+
+// Workgroup b runs on XCD b % 8 (round-robin dispatch), so a fixed bucket per XCD gives the query heads
+// of one key/value head one L2, but also ties an XCD's work to its bucket's.  Vertical-slash heads
+// keep very different numbers of tiles (and block-sparse mates unite to different numbers), so the
+// XCD with the heaviest bucket ran alone at the end.  The buckets therefore move on by one XCD every
+// kRotate items of a bucket: long enough stays for the items that share tiles, short enough for an
+// even mix.  Measured with 8 key/value heads, fixed buckets -> rotation: vertical-slash n = 32768
+// (1000, 512) 5.24 -> 2.65 ms, (1000, 6096) 8.55 -> 7.72 ms, n = 16384 1.59 -> 1.15 ms, n = 4096 192
+// -> 176 us (every item: 3.62, 8.50, 1.33 ms and 186 us; every 64 items: 2.77, 7.82, 1.21 ms and
+// 185 us); block-sparse n = 131072 18.3 -> 15.2 ms, n = 32768 3.70 -> 3.20 ms, n = 4096 119 -> 117 us
+// (every 16 items: 15.4, 3.25 ms and 115 us).  Dense and A-shape heads weigh the same.
+template <int PAT>
+constexpr int kRotate = PAT == P_VS ? 16 : PAT == P_BS ? 64 : 0;
+
 struct AttnDirect {
   AttnArgs a;
   int nu, tiles, nsplit, nseg;
@@ -948,7 +962,9 @@ __global__ void __launch_bounds__(256, 2) attn_fwd_kernel(const AttnDirect p) {
     const int x = (int)blockIdx.x;
     int k = 0;
     while (k + 1 < p.nseg && x >= p.pos[k + 1]) ++k;
-    const int rem = x - p.pos[k], turn = rem / p.na[k], j = rem - turn * p.na[k];
+    const int rem = x - p.pos[k], turn = rem / p.na[k];
+    int j = rem - turn * p.na[k];
+    if constexpr (kRotate<PAT> > 0) j = (j + turn / kRotate<PAT>) % p.na[k];
     const int b = __builtin_amdgcn_readfirstlane((int)(p.act[k] >> (4 * j)) & 7);
     const int i = p.first[k] + turn;  // item i of bucket b
     // longest query tiles first, then the bucket's units, then the pieces of an item
@@ -1323,8 +1339,8 @@ static void pair_units(const rs_unit *units, int nunits, int group, std::vector<
 // dispatch places workgroup b on XCD b % 8, so the query heads sharing one K/V stream
 // share one XCD's L2), longest query tiles first within a bucket.  Items of a unit with a
 // mate are 64-row query blocks, others bm-row query tiles (bm = 128); units taken along by a
-// mate have none.  Pieces of a split item follow one another.
-static void build_order(const rs_unit *units, int nunits, int group, int bm, const std::vector<int> &mate,
+// mate have none.  Pieces of a split item follow one another.  rotate: as kRotate.
+static void build_order(const rs_unit *units, int nunits, int group, int bm, int rotate, const std::vector<int> &mate,
                         const std::vector<SplitRule> &split, std::vector<int> &order) {
   std::vector<std::vector<std::pair<int, int>>> buckets(8);  // (-first row / 64, item)
   for (int u = 0; u < nunits; ++u) {
@@ -1343,9 +1359,12 @@ static void build_order(const rs_unit *units, int nunits, int group, int bm, con
     mx = std::max(mx, b.size());
   }
   order.clear();
-  for (size_t i = 0; i < mx; ++i)
+  for (size_t i = 0; i < mx; ++i) {
+    int act[8], na = 0;
     for (int b = 0; b < 8; ++b)
-      if (i < buckets[b].size()) order.push_back(buckets[b][i].second);
+      if (i < buckets[b].size()) act[na++] = b;
+    for (int j = 0; j < na; ++j) order.push_back(buckets[act[(j + (rotate ? i / rotate : 0)) % na]][i].second);
+  }
 }
 
 template <int D, int PAT, typename InT, bool VT>
@@ -1548,7 +1567,8 @@ rs_status attn_launch(const rs_qkv *qkv, float scale, const rs_unit *units, int3
   } else {
     // the list in the workspace: [DevUnit x nunits][order], and the split items by partial slot
     p.nu = 0;
-    build_order(units, nunits, group, bm, mate, split, order);
+    const int rotate = fam == RS_VSLASH ? kRotate<P_VS> : fam == RS_BSPARSE ? kRotate<P_BS> : 0;
+    build_order(units, nunits, group, bm, rotate, mate, split, order);
     Arena ar(ws, ws_bytes);
     d_units = ar.take<DevUnit>((size_t)nunits);
     int *d_order = ar.take<int>(order.size());
