@@ -313,7 +313,7 @@ rs_status rs_route_layer_device_noalloc(const rs_route_in *in, const rs_route_cf
  *  - Work lists are built on the device by a planning kernel: query tiles bucketed by
  *    key/value head, longest first.
  *  - O and lse equal those of one rs_sparse_attn_prefill / rs_dense_attn_prefill call per
- *    (pattern, budget) group.
+ *    (pattern, budget) group, each call given the workspace its size query asks for.
  *  - `units` is the layer's host unit list; `slot` is the unit's row in `idx`, and the
  *    unit's `cand` field is ignored.
  *  - Grids are sized for every unit picking the family; surplus workgroups exit at once.
@@ -346,7 +346,11 @@ rs_status rs_transpose_v(const rs_qkv *qkv, void *vt, rs_stream stream);
  * log sum over S_i of exp(l_ij) (natural log; -inf for an empty row).  Sparse calls read
  * the index set built by rs_build_indices with the same grid (A-shape needs none and
  * accepts idx == NULL).  Units of different calls may run concurrently only if they write
- * disjoint rows. */
+ * disjoint rows.
+ * The workspace holds the work lists, the partial results of items split along their keys and
+ * bf16 copies of fp32 inputs.  The size query counts all three; with a workspace that has room
+ * for the lists but not for the rest, items run unsplit (their rows then differ in the last
+ * bits, as the partial sums add in another order) and fp32 inputs are rounded per tile. */
 size_t rs_attn_workspace_size(const rs_qkv *qkv, const rs_unit *units, int32_t nunits);
 rs_status rs_sparse_attn_prefill(const rs_qkv *qkv, const rs_unit *units, int32_t nunits,
                                  const rs_candidate *grid, int32_t ncand,

@@ -10,7 +10,10 @@
 //
 // Work decomposition: one workgroup = one 128-row query tile of one unit, 4 waves of 32
 // rows each; two workgroups share a CU (<= 256 VGPRs, 64 KB LDS each), so one's softmax
-// overlaps the other's matrix work.  Keys stream through two LDS buffers in tiles of 64
+// overlaps the other's matrix work.  Dense and vertical-slash items whose launch would leave
+// the GPU idle are split along their keys, and a second kernel merges the pieces' partial
+// results; fp32 inputs are first rounded to bf16 copies when the workspace has room for them.
+// Keys stream through two LDS buffers in tiles of 64
 // (contiguous keys, or gathered vertical columns for vertical-slash): the next tile is
 // copied global -> LDS directly (global_load_lds_dwordx4, no registers) while the current
 // one is computed, with one barrier per tile.  K and V tiles are row-major with an XOR
