@@ -1373,7 +1373,10 @@ static int probe_range(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, 
 
 static int row_pairs(int rows) { return ((rows + 31) / 32 + 1) / 2; }
 
-// Workspace of a scores call (coverage: of a coverage call) with ranges of `range` keys.
+// Workspace of a call with ranges of `range` keys.  Its size is not monotone in the range: shorter
+// ranges hold more partial results per sampled row, longer ones round the diagonals (nchunks * range
+// floats per unit) further up.  A configuration without recent rows has no diagonals, one without
+// sampled rows (block means only) no partial results at all.
 struct ProbeWs {
   ProbeUnit *units;
   int4 *groups;
@@ -1387,7 +1390,7 @@ static ProbeWs probe_ws_layout(void *ws, const rs_qkv *qkv, int32_t nunits, cons
   ProbeWs w{};
   w.units = ar.take<ProbeUnit>(nunits);
   w.groups = ar.take<int4>(nunits);
-  w.diag_part = ar.take<float>((size_t)nunits * nchunks * (range + rmax));
+  w.diag_part = ar.take<float>(cfg->r_rec > 0 ? (size_t)nunits * nchunks * (range + rmax) : 0);
   w.ent_part = ar.take<float>((size_t)nunits * nchunks * rmax);
   w.loc_part = ar.take<float>((size_t)nunits * nchunks * rmax);
   w.max_part = ar.take<float>((size_t)nunits * nchunks * rmax);
@@ -1405,7 +1408,8 @@ size_t probe_ws_bytes(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, c
   if (qkv->n < 1 || qkv->hq < 1 || qkv->hkv < 1) return 256;
   const int r1 = probe_range(qkv, units, nunits, 1, kWantScores);
   const int r2 = probe_range(qkv, units, nunits, row_pairs(rmax_of(cfg)), kWantCover);
-  return probe_ws_layout(nullptr, qkv, nunits, cfg, std::min(r1, r2)).bytes;
+  return std::max(probe_ws_layout(nullptr, qkv, nunits, cfg, r1).bytes,
+                  probe_ws_layout(nullptr, qkv, nunits, cfg, r2).bytes);
 }
 
 template <int D, typename InT>
@@ -1452,16 +1456,19 @@ rs_status probe_launch(const rs_qkv *qkv, float scale, const rs_unit *units, int
   const int rmax = rmax_of(cfg);
   const int nb = (qkv->n + 63) / 64;
   const bool cover = idx != nullptr;
-  // a workspace sized for longer ranges is used with those
-  int range = cover ? probe_range(qkv, units, nunits, row_pairs(rmax), kWantCover)
-                    : probe_range(qkv, units, nunits, 1, kWantScores);
-  ProbeWs w = probe_ws_layout(ws, qkv, nunits, cfg, range);
-  while (ws && ws_bytes < w.bytes && range < kMaxRange) {
-    range <<= 1;
-    w = probe_ws_layout(ws, qkv, nunits, cfg, range);
-  }
-  if (!ws || ws_bytes < w.bytes)
-    return fail(RS_ERR_WORKSPACE, "probe workspace too small: need " + std::to_string(w.bytes));
+  // a workspace without room for the call's own range is used with the next longer one that fits,
+  // else with the next shorter one
+  const int own = cover ? probe_range(qkv, units, nunits, row_pairs(rmax), kWantCover)
+                        : probe_range(qkv, units, nunits, 1, kWantScores);
+  const size_t need = probe_ws_layout(nullptr, qkv, nunits, cfg, own).bytes;
+  auto fits = [&](int r) { return ws && probe_ws_layout(nullptr, qkv, nunits, cfg, r).bytes <= ws_bytes; };
+  int range = own;
+  while (range <= kMaxRange && !fits(range)) range <<= 1;
+  if (range > kMaxRange)
+    for (range = own >> 1; range >= kMinRange && !fits(range);) range >>= 1;
+  if (range < kMinRange)
+    return fail(RS_ERR_WORKSPACE, "probe workspace too small: need " + std::to_string(need));
+  const ProbeWs w = probe_ws_layout(ws, qkv, nunits, cfg, range);
   const int nchunks = (qkv->n + range - 1) / range;
   ProbeUnit *d_units = w.units;
   int4 *d_groups = w.groups;
