@@ -1121,8 +1121,7 @@ rs_status attn_cvt_launch(const rs_qkv *qkv, const rs_unit *units, int32_t nunit
 }
 
 // ---- merge of split items ------------------------------------------------------------------
-// grid (slots, or items with a list in the arguments; 8), 256 threads: 16 rows of an item per
-// workgroup, 16 threads per row.  Piece p of
+// grid (items, 8), 256 threads: 16 rows of an item per workgroup, 16 threads per row.  Piece p of
 // a row holds O_p relative to its own running max m_p: with M the largest and w_p = exp(m_p - M),
 // O = sum w_p O_p / sum w_p l_p, in piece order (a fixed order: the result is deterministic).  A
 // piece that kept no key of the row has l_p = 0 and m_p = -inf.  Bound by reading the pieces.
@@ -1136,19 +1135,20 @@ __global__ void __launch_bounds__(256) attn_merge_kernel(const DevUnit *units, c
                                                          const MergeDirect m, bf16 *o, long long so_h, long long so_t,
                                                          float *lse, int n, float c, float scale) {
   constexpr int EPT = D / 16, BM = 128;  // elements per thread, rows of an item
-  int slot0 = blockIdx.x, qt, head, s0, s1;
+  int slot0, qt, head, s0, s1;
   if (m.tiles > 0) {
-    const int u = slot0 / m.tiles;
-    qt = slot0 - u * m.tiles;
-    slot0 *= m.nsplit;
+    const int u = (int)blockIdx.x / m.tiles;
+    qt = (int)blockIdx.x - u * m.tiles;
+    slot0 = (int)blockIdx.x * m.nsplit;
     head = m.head[u];
     s0 = m.s0;
     s1 = m.s1;
   } else {
-    const int item = parts.items[slot0];
+    const int item = parts.items[blockIdx.x];
     if (item < 0) return;
     const DevUnit U = units[item >> 16];
     qt = item & 0xfff;
+    slot0 = U.pbase + qt * U.nsplit;
     head = U.head;
     s0 = U.s0;
     s1 = U.s1;
@@ -1219,8 +1219,8 @@ static rs_status merge_launch(const rs_qkv *qkv, float scale, const DevUnit *d_u
 }
 
 rs_status attn_merge_launch(const rs_qkv *qkv, float scale, const DevUnit *d_units, const AttnParts &parts,
-                            int slots, void *o, int64_t so_h, int64_t so_t, float *lse, hipStream_t st) {
-  return merge_launch(qkv, scale, d_units, parts, MergeDirect{}, slots, o, so_h, so_t, lse, st);
+                            int nitems, void *o, int64_t so_h, int64_t so_t, float *lse, hipStream_t st) {
+  return merge_launch(qkv, scale, d_units, parts, MergeDirect{}, nitems, o, so_h, so_t, lse, st);
 }
 
 // ---- V^T: [hkv][d][npad] bf16, keys permuted within groups of 16 ---------------------------
@@ -1304,7 +1304,7 @@ size_t attn_ws_bytes(const rs_qkv *qkv, const rs_unit *units, int32_t nunits) {
   size_t items = 0, slots = 0;
   for (int i = 0; i < nunits; ++i) {
     const rs_unit &u = units[i];
-    const int s = qkv && u.s0 >= 0 && u.s1 > u.s0 && qkv->hq > 0 ? attn_split_slots(qkv->hq, qkv->d, u.s0, u.s1) : 0;
+    const int s = qkv && u.s0 >= 0 && u.s1 > u.s0 && qkv->hq > 0 ? attn_split_slots(qkv->hq, qkv->d, qkv->n, u.s0, u.s1) : 0;
     items += std::max<size_t>((size_t)tiles_of(u, 128), (size_t)s);
     slots += (size_t)s;
   }
@@ -1517,7 +1517,7 @@ rs_status attn_launch(const rs_qkv *qkv, float scale, const rs_unit *units, int3
   size_t slots = 0, items = 0;
   for (int u = 0; u < nunits; ++u) {
     if (mate[u] == -2) continue;
-    split[u] = attn_split(qkv->hq, qkv->d, units[u].s0, units[u].s1, fam);
+    split[u] = attn_split(qkv->hq, qkv->d, qkv->n, units[u].s0, units[u].s1, fam);
     const size_t nt = (size_t)tiles_of(units[u], mate[u] >= 0 ? 64 : bm);
     if (split[u].nsplit > 1) slots += nt * split[u].nsplit;
     items += nt * split[u].nsplit;
@@ -1555,12 +1555,14 @@ rs_status attn_launch(const rs_qkv *qkv, float scale, const rs_unit *units, int3
   AttnDirect p{};
   p.a = attn_args(qkv, scale, fam, idx, parts, o, so_h, so_t, lse);
   MergeDirect md{};
+  int nmerge = 0;  // items that may have pieces
   DevUnit *d_units = nullptr;
   if (direct_list(units, nunits, group, mate, du, p)) {
     md = MergeDirect{p.tiles, p.nsplit, p.u[0].s0, p.u[0].s1, {}};
     for (int u = 0; u < p.nu; ++u) md.head[u] = p.u[u].head;
+    nmerge = p.nu * p.tiles;
   } else {
-    // the list in the workspace: [DevUnit x nunits][order], and the split items by partial slot
+    // the list in the workspace: [DevUnit x nunits][order], and the split items
     p.nu = 0;
     const int rotate = fam == RS_VSLASH ? kRotate<P_VS> : fam == RS_BSPARSE ? kRotate<P_BS> : 0;
     build_order(units, nunits, group, bm, rotate, mate, split, order);
@@ -1573,10 +1575,11 @@ rs_status attn_launch(const rs_qkv *qkv, float scale, const rs_unit *units, int3
     memcpy(stage.data() + off_order, order.data(), order.size() * sizeof(int));
     RS_HIP(hipMemcpyAsync(ws, stage.data(), stage.size(), hipMemcpyHostToDevice, st));
     if (slots > 0) {
-      std::vector<int> h_items(slots, -1);
+      std::vector<int> h_items;
       for (int u = 0; u < nunits; ++u)
         if (split[u].nsplit > 1)
-          for (int t = 0; t < tiles_of(units[u], bm); ++t) h_items[du[u].pbase + t * split[u].nsplit] = (u << 16) | t;
+          for (int t = 0; t < tiles_of(units[u], bm); ++t) h_items.push_back((u << 16) | t);
+      nmerge = (int)h_items.size();
       RS_HIP(hipMemcpyAsync(parts.items, h_items.data(), h_items.size() * sizeof(int), hipMemcpyHostToDevice, st));
     }
     p.a.units = d_units;
@@ -1586,8 +1589,7 @@ rs_status attn_launch(const rs_qkv *qkv, float scale, const rs_unit *units, int3
                                      : launch_d<64>(fam, qkv->dtype, p, (int)items, st);
   if (e != hipSuccess) return hip_check(e, "attention kernel launch");
   if (slots > 0)
-    return merge_launch(qkv, scale, d_units, parts, md, md.tiles > 0 ? p.nu * p.tiles : (int)slots, o, so_h, so_t, lse,
-                        st);
+    return merge_launch(qkv, scale, d_units, parts, md, nmerge, o, so_h, so_t, lse, st);
   return RS_OK;
 }
 

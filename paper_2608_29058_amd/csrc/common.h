@@ -63,50 +63,56 @@ struct DevUnit {
 // of at least ptiles 64-key tiles, each a workgroup of its own, merged by attn_merge_kernel.  The
 // rule sees the unit and the layer's shape only, never the rest of the launch, so that a unit's
 // result does not depend on the units it is launched with.
+//   * Only units that end with the sequence (s1 = n) are split: a whole prompt, a chunk of a chunked
+//     prefill, the last segment of a layer cut into segments.  Where other segments are launched with
+//     it, they fill the chip by themselves and need neither pieces nor room for them, and a list holds
+//     at most one such unit per head, which bounds the partial results of a launch by
+//     kSplitSlotsMax items' (98 MiB at d = 128).
 //   * The chip holds 512 workgroups of the attention kernel.  Dense items of all heads over the
-//     unit's rows that would leave more than half of them idle are split until they fill them
-//     (512 rows x 32 heads at 64K keys: 1195 us in one piece, 531 us in four).
+//     unit's rows that would leave more than half of them idle (at most 256 items) are split until
+//     they fill them (512 rows x 32 heads at 64K keys: 1195 us in one piece, 531 us in four).
 //   * Vertical-slash items have very different lengths (a diffuse head keeps several times the tiles
-//     of a local one), so they are split below four rounds of workgroups (2048 rows x 32 heads at
-//     50K keys: 1759 -> 1275 us with up to four pieces and the mask words fetched once per wave,
-//     which alone gives 1.17x).
+//     of a local one), so they are split into up to three rounds of workgroups (at most 768 items):
+//     2048 rows x 32 heads at 50K keys took 1759 us in one piece and 1275 us in up to four with the mask
+//     words fetched once per wave, which alone gives 1.17x; the whole call (probe, indices, attention)
+//     of the same shape on other inputs takes 587 us with four pieces and 566 us with three.
 //   * A piece writes and the merge reads d + 2 floats per row: pieces are long enough (32 and 64
 //     tiles) to make that small, or 8 tiles where all partial results together stay in cache.
 // A-shape lists are short and block-sparse ones are even: neither is split.
 struct SplitRule {
   int nsplit, ptiles;
 };
-constexpr int kMaxSplit = 16;
-__host__ __device__ inline SplitRule attn_split(int hq, int d, int s0, int s1, int fam) {
-  if (fam != RS_DENSE && fam != RS_VSLASH) return SplitRule{1, 1};
+constexpr int kMaxSplit = 16, kSplitSlotsMax = 1536;
+__host__ __device__ inline SplitRule attn_split(int hq, int d, int n, int s0, int s1, int fam) {
+  if ((fam != RS_DENSE && fam != RS_VSLASH) || s1 < n) return SplitRule{1, 1};
   const int par = hq * ((s1 - 1) / 128 - s0 / 128 + 1);  // items of the unit's rows over all heads
-  int want = (fam == RS_DENSE ? 512 : 2048) / par;
+  int want = (fam == RS_DENSE ? 512 : kSplitSlotsMax) / par;
   want = want < kMaxSplit ? want : kMaxSplit;
   if (want < 2) return SplitRule{1, 1};
   const bool small = (long long)hq * (s1 - s0) * d * 4 * want <= 16ll << 20;
   const int ptiles = small ? 8 : fam == RS_DENSE ? 32 : 64, most = ((s1 + 63) / 64) / ptiles;
-  const int n = want < most ? want : most;
-  return SplitRule{n < 1 ? 1 : n, ptiles};
+  const int pieces = want < most ? want : most;
+  return SplitRule{pieces < 1 ? 1 : pieces, ptiles};
 }
 // Partial slots (one per item and piece) of a unit, whatever its family turns out to be; 0 when it
 // never splits.
-__host__ __device__ inline int attn_split_slots(int hq, int d, int s0, int s1) {
-  const int a = attn_split(hq, d, s0, s1, RS_DENSE).nsplit, b = attn_split(hq, d, s0, s1, RS_VSLASH).nsplit;
+__host__ __device__ inline int attn_split_slots(int hq, int d, int n, int s0, int s1) {
+  const int a = attn_split(hq, d, n, s0, s1, RS_DENSE).nsplit, b = attn_split(hq, d, n, s0, s1, RS_VSLASH).nsplit;
   const int m = a > b ? a : b;
   return m > 1 ? m * ((s1 - 1) / 128 - s0 / 128 + 1) : 0;
 }
 // Partial results of split items.  Per slot and row of the item: O (fp32, unnormalised), running max
-// and sum; n: the pieces taken, at an item's first slot; items: per first slot the item
-// (unit << 16 | query tile), -1 elsewhere.
+// and sum; n: the pieces taken, at an item's first slot; items: (unit << 16 | query tile) per query tile
+// of the units that may split, -1 where the unit's family turned out not to.
 struct AttnParts {
   float *o, *ml;
   int *n, *items;
 };
 size_t attn_parts_bytes(int d, size_t slots);
 AttnParts attn_parts_at(void *p, int d, size_t slots);
-// Merges the pieces of every split item.
+// Merges the pieces of the split items among parts.items[0 .. nitems).
 rs_status attn_merge_launch(const rs_qkv *qkv, float scale, const DevUnit *d_units, const AttnParts &parts,
-                            int slots, void *o, int64_t so_h, int64_t so_t, float *lse, hipStream_t st);
+                            int nitems, void *o, int64_t so_h, int64_t so_t, float *lse, hipStream_t st);
 
 // fp32 Q, K and V rounded to bf16 in the workspace before the attention, as the kernels would on
 // load: rows the units read, [head][token][d].  bytes: 0 for bf16 inputs.

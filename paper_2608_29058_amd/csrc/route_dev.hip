@@ -492,8 +492,8 @@ struct PlanArgs {
   int *order;       // [4][max_items], bucket-major
   int max_items;
   int *qsize, *qoff, *qcount;  // [4][8] each
-  int hq, d;
-  int *items;  // split items by partial slot (AttnParts::items), or NULL: no item is split
+  int hq, d, n;
+  int *items;  // split items (AttnParts::items), or NULL: no item is split
 };
 
 // Exclusive prefix sum over the workgroup (1024 threads) in thread order; *tot: the sum.
@@ -535,30 +535,34 @@ __global__ void __launch_bounds__(1024) plan_kernel(const PlanArgs a) {
   // (each split into sp pieces, dense and vertical-slash)
   __shared__ uint32_t sIt[kRouteMaxUnits];  // k0 | n << 13 | sh << 26 | sp << 27
   __shared__ int sPb[kRouteMaxUnits];       // first partial slot of the unit
+  __shared__ int sIb[kRouteMaxUnits];       // first entry of its query tiles among the items that may split
   __shared__ int sWave[16];
   const int U = a.U;
-  int nl = 0, before = 0, slots = 0;
+  int nl = 0, before = 0, slots = 0, mayb = 0;
   for (int u0 = 0; u0 < U; u0 += NT) {
     const int u = u0 + tid;
     bool mine = false, lost = false;
-    int tiles = 0, ps = 0;
+    int tiles = 0, ps = 0, nt = 0;
     rs_unit un{};
     if (u < U) {
       un = a.units[u];
       const int c = a.choice[u], bu = (un.head / a.group) & 7;
       const bool valid = c >= 0 && c < a.C;
       mine = bu == b && valid && a.fam[c] == f;
-      lost = bu == b && !valid && f == RS_DENSE;  // not computed: its partial slots hold no item
+      lost = bu == b && !valid && f == RS_DENSE;  // not computed: none of its tiles is a split item
       // query tiles in the buckets before this one, as many times as any family may split them
-      if (a.items) ps = attn_split_slots(a.hq, a.d, un.s0, un.s1);
-      tiles = bu < b ? max(((un.s1 - 1) >> 7) - (un.s0 >> 7) + 1, ps) : 0;
+      nt = ((un.s1 - 1) >> 7) - (un.s0 >> 7) + 1;
+      if (a.items) ps = attn_split_slots(a.hq, a.d, a.n, un.s0, un.s1);
+      tiles = bu < b ? max(nt, ps) : 0;
     }
-    int tot, pb = 0;
+    int tot, pb = 0, ib = 0;
     if (a.items) {
       pb = slots + block_excl_scan(ps, sWave, &tot);
       slots += tot;
-      if (lost)
-        for (int x = 0; x < ps; ++x) a.items[pb + x] = -1;
+      ib = mayb + block_excl_scan(ps > 0 ? nt : 0, sWave, &tot);
+      mayb += tot;
+      if (lost && ps > 0)
+        for (int x = 0; x < nt; ++x) a.items[ib + x] = -1;
     }
     const int at = nl + block_excl_scan(mine ? 1 : 0, sWave, &tot);
     if (mine) {
@@ -568,6 +572,7 @@ __global__ void __launch_bounds__(1024) plan_kernel(const PlanArgs a) {
       sS1[at] = un.s1;
       sMate[at] = -1;
       sPb[at] = pb;
+      sIb[at] = ps > 0 ? ib : -1;
     }
     nl += tot;
     block_excl_scan(tiles, sWave, &tot);
@@ -608,14 +613,12 @@ __global__ void __launch_bounds__(1024) plan_kernel(const PlanArgs a) {
       const int u = sU[x], c = a.choice[u], m = sMate[x];
       const int sh = m >= 0 ? 0 : 1, lg = 6 + sh;  // log2 of an item's rows
       n = m == -2 ? 0 : ((sS1[x] - 1) >> lg) - (sS0[x] >> lg) + 1;
-      const SplitRule sp = a.items ? attn_split(a.hq, a.d, sS0[x], sS1[x], f) : SplitRule{1, 1};
+      const SplitRule sp = a.items ? attn_split(a.hq, a.d, a.n, sS0[x], sS1[x], f) : SplitRule{1, 1};
       sIt[x] = (uint32_t)((sS0[x] >> lg) << sh) | ((uint32_t)n << 13) | ((uint32_t)sh << 26) |
                ((uint32_t)sp.nsplit << 27);
-      if (a.items) {
-        const int ps = attn_split_slots(a.hq, a.d, sS0[x], sS1[x]);
-        for (int y = 0; y < ps; ++y)
-          a.items[sPb[x] + y] = sp.nsplit > 1 && y % sp.nsplit == 0 && y / sp.nsplit < n
-                                    ? ((f * U + u) << 16) | (y / sp.nsplit) : -1;
+      if (a.items && sIb[x] >= 0) {
+        const int nt = ((sS1[x] - 1) >> 7) - (sS0[x] >> 7) + 1;
+        for (int t = 0; t < nt; ++t) a.items[sIb[x] + t] = sp.nsplit > 1 ? ((f * U + u) << 16) | t : -1;
       }
       n *= sp.nsplit;
       if (n > 0)
@@ -761,23 +764,28 @@ static size_t routed_list_bytes(int32_t nunits, size_t items) {
   return ar.off + 256;  // (rounded down to 256 bytes: at or past the lists' end)
 }
 
-// Most items of a family and partial slots of the units; split: items may be split along the keys.
-static void routed_counts(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, bool split, size_t *items,
-                          size_t *slots) {
-  *items = *slots = 0;
+// Most items of a family, partial slots of the units and query tiles that may have pieces; split:
+// items may be split along the keys.
+struct RoutedCounts {
+  size_t items = 0, slots = 0, mayb = 0;
+};
+static RoutedCounts routed_counts(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, bool split) {
+  RoutedCounts c;
   for (int i = 0; i < nunits; ++i) {
     const rs_unit &u = units[i];
+    const int nt = (u.s1 - 1) / 128 - u.s0 / 128 + 1;
     const int s = split && qkv && qkv->hq > 0 && u.s0 >= 0 && u.s1 > u.s0
-                      ? attn_split_slots(qkv->hq, qkv->d, u.s0, u.s1) : 0;
-    *items += (size_t)std::max((u.s1 - 1) / 128 - u.s0 / 128 + 1, s);
-    *slots += (size_t)s;
+                      ? attn_split_slots(qkv->hq, qkv->d, qkv->n, u.s0, u.s1) : 0;
+    c.items += (size_t)std::max(nt, s);
+    c.slots += (size_t)s;
+    if (s > 0) c.mayb += (size_t)nt;
   }
+  return c;
 }
 
 size_t routed_attn_ws_bytes(const rs_qkv *qkv, const rs_unit *units, int32_t nunits) {
-  size_t items, slots;
-  routed_counts(qkv, units, nunits, true, &items, &slots);
-  return routed_list_bytes(nunits, items) + attn_parts_bytes(qkv ? qkv->d : 0, slots) +
+  const RoutedCounts c = routed_counts(qkv, units, nunits, true);
+  return routed_list_bytes(nunits, c.items) + attn_parts_bytes(qkv ? qkv->d : 0, c.slots) +
          attn_cvt_bytes(qkv, units, nunits);
 }
 
@@ -787,14 +795,14 @@ rs_status routed_attn_launch(const rs_qkv *qkv, float scale, const rs_unit *unit
                              void *const *events, hipStream_t st) {
   if (nunits == 0) return RS_OK;
   if (nunits > kRouteMaxUnits) return fail(RS_ERR_UNSUPPORTED, "routed attention supports nunits <= 2048");
-  size_t items, slots;
-  routed_counts(qkv, units, nunits, true, &items, &slots);
-  size_t need = routed_list_bytes(nunits, items);
+  RoutedCounts cn = routed_counts(qkv, units, nunits, true);
+  size_t need = routed_list_bytes(nunits, cn.items);
   // items are split where the workspace holds their partial results
-  if (slots > 0 && (!ws || ((uintptr_t)ws & 15) || ws_bytes < need + attn_parts_bytes(qkv->d, slots))) {
-    routed_counts(qkv, units, nunits, false, &items, &slots);
-    need = routed_list_bytes(nunits, items);
+  if (cn.slots > 0 && (!ws || ((uintptr_t)ws & 15) || ws_bytes < need + attn_parts_bytes(qkv->d, cn.slots))) {
+    cn = routed_counts(qkv, units, nunits, false);
+    need = routed_list_bytes(nunits, cn.items);
   }
+  const size_t items = cn.items, slots = cn.slots;
   if (!ws || ws_bytes < need)
     return fail(RS_ERR_WORKSPACE, "routed attention workspace too small: need " + std::to_string(need) + " bytes");
   AttnParts parts{};
@@ -832,6 +840,7 @@ rs_status routed_attn_launch(const rs_qkv *qkv, float scale, const rs_unit *unit
   p.max_items = (int)items;
   p.hq = qkv->hq;
   p.d = qkv->d;
+  p.n = qkv->n;
   p.items = slots > 0 ? parts.items : nullptr;
   p.qsize = d_q;
   p.qoff = d_q + 32;
@@ -853,7 +862,7 @@ rs_status routed_attn_launch(const rs_qkv *qkv, float scale, const rs_unit *unit
   if (!events) {  // every family in one launch
     rs_status s = attn_launch_queues(qkv, scale, -1, idx, p.dunits, p.order, qs, nblocks, parts, o, so_h, so_t, lse, st);
     if (s == RS_OK && slots > 0)
-      s = attn_merge_launch(qkv, scale, p.dunits, parts, (int)slots, o, so_h, so_t, lse, st);
+      s = attn_merge_launch(qkv, scale, p.dunits, parts, (int)cn.mayb, o, so_h, so_t, lse, st);
     return s;
   }
   // one launch per family, timed apart; dense first: its items are the longest
@@ -866,7 +875,7 @@ rs_status routed_attn_launch(const rs_qkv *qkv, float scale, const rs_unit *unit
       if (s != RS_OK) return s;
     }
     if (f == RS_VSLASH && slots > 0) {  // the two families with split items are launched
-      rs_status s = attn_merge_launch(qkv, scale, p.dunits, parts, (int)slots, o, so_h, so_t, lse, st);
+      rs_status s = attn_merge_launch(qkv, scale, p.dunits, parts, (int)cn.mayb, o, so_h, so_t, lse, st);
       if (s != RS_OK) return s;
     }
     RS_HIP(hipEventRecord((hipEvent_t)events[1 + k], st));

@@ -70,7 +70,6 @@ class RoutedLayer:
         self.tables = None   # device unit tables (rs_unit_table_init), built with the first qkv()
         self.use_tables = use_tables
         self._ws = None
-        self._ws_routed = None
         self.t_table = None
         self.edges = None
         self.t_probe_us = 0.0
@@ -97,7 +96,8 @@ class RoutedLayer:
         if self._ws is None:
             need = max(_rs.rs_probe_workspace_size(qkv, self.units, self.nunits, self.cfg),
                        _rs.rs_build_indices_workspace_size(self.pb, self.g, self.ncand),
-                       _rs.rs_attn_workspace_size(qkv, self.units, self.nunits))
+                       _rs.rs_attn_workspace_size(qkv, self.units, self.nunits),
+                       _rs.rs_routed_attn_workspace_size(qkv, self.units, self.nunits))
             self._ws = _rs.workspace(need)
         return self._ws
 
@@ -148,10 +148,8 @@ class RoutedLayer:
     def run_routed(self, qkv, lse=None, family_events=None):
         """All units with the device route's choices: one rs_routed_attn_prefill call
         (``family_events``: five timing events around its per-family launches)."""
-        if self._ws_routed is None:
-            self._ws_routed = _rs.workspace(_rs.rs_routed_attn_workspace_size(qkv, self.units, self.nunits))
         _rs.rs_routed_attn_prefill(qkv, self.units, self.nunits, self.g, self.ncand, self.ib, self.rb.choice,
-                                   self.o, lse, self._ws_routed, events=family_events)
+                                   self.o, lse, self.workspace(qkv), events=family_events)
 
     def group_units(self, cand, unit_idx):
         return _rs.make_units([(self.unit_list[u][0], self.unit_list[u][1], self.unit_list[u][2], cand, u)
