@@ -12,7 +12,8 @@
 // rows each; two workgroups share a CU (<= 256 VGPRs, 64 KB LDS each), so one's softmax
 // overlaps the other's matrix work.  Dense and vertical-slash items whose launch would leave
 // the GPU idle are split along their keys, and a second kernel merges the pieces' partial
-// results; fp32 inputs are first rounded to bf16 copies when the workspace has room for them.
+// results; fp32 inputs that a call reads often enough are first rounded to bf16 copies when the
+// workspace has room for them.
 // Keys stream through two LDS buffers in tiles of 64
 // (contiguous keys, or gathered vertical columns for vertical-slash): the next tile is
 // copied global -> LDS directly (global_load_lds_dwordx4, no registers) while the current
@@ -1043,79 +1044,196 @@ __global__ void __launch_bounds__(256, 2) attn_fwd_layer_kernel(const AttnArgs a
 }
 
 // ---- fp32 inputs -----------------------------------------------------------------------------
-// One row of one head per d / 8 threads: 8 elements each, rounded as load8 does.  grid (row blocks,
-// hq + 2 hkv).  The attention kernels copy bf16 tiles straight into LDS; fp32 tiles go through
-// registers, and the load, its wait and the rounding then sit in front of every tile step (once per
-// query tile instead of once per layer).  Bound by memory: 74 MB read and
-// written in 12.6 us (5.8 TB/s) for 16 heads of 4000 tokens, d = 64, whose attention took 104 us with
-// fp32 tiles and takes 78 us with the conversion.
-struct CvtArgs {
-  const float *src[3];
-  long long sh[3], st[3];
-  bf16 *dst[3];
-  int r0[3], rows[3], heads[3];
-  int n, d, lgc;  // lgc: log2 of 8-element chunks per row
+// The attention kernels copy bf16 tiles straight into LDS; fp32 tiles go through registers, and the
+// load, its wait and the rounding then sit in front of every tile step.  Where a call reads its inputs
+// often enough, they are rounded once instead, as load8 does it (the results are the same bits): the
+// query rows of the heads that the units name, and their key/value heads up to the last key that a
+// unit sees.  One 8-element chunk per thread, d / 8 threads per row; grid (row blocks, heads), or one
+// row of workgroups that look their head up where the heads' rows are uneven (the search costs 1 us of
+// 13 for 48 heads).  Bound by memory: 302 MB read and written in 44 us (6.9 TB/s) for
+// 32/8 heads of 8192 tokens, d = 128.
+constexpr int kCvtHeads = 192;  // heads of one launch (more: several launches)
+struct CvtArray {                  // Q, K or V
+  const float *src;
+  bf16 *dst;             // of head 0, token 0 (inside the copy for the heads and rows below only)
+  long long sh, st, dh;  // element strides: heads and tokens of the input, heads of the copy
 };
+struct CvtHead {
+  int which, row0, rows, start;  // 4 * head + array, its rows, its first workgroup
+};
+struct CvtArgs {
+  CvtArray x[3];
+  int d, lgc, nheads, blocks;  // lgc: log2 of 8-element chunks per row
+  CvtHead head[kCvtHeads];
+};
+static_assert(sizeof(CvtArgs) <= 4096, "kernel arguments");
 __global__ void __launch_bounds__(256) attn_cvt_kernel(const CvtArgs a) {
-  int h = blockIdx.y, k = 0;
-  while (h >= a.heads[k]) h -= a.heads[k++];
-  const int x = blockIdx.x * 256 + threadIdx.x, r = x >> a.lgc, c = x & ((1 << a.lgc) - 1);
-  if (r >= a.rows[k]) return;
-  const float *s = a.src[k] + (long long)h * a.sh[k] + (long long)(a.r0[k] + r) * a.st[k] + 8 * c;
-  *(u32x4 *)(a.dst[k] + ((long long)h * a.rows[k] + r) * a.d + 8 * c) = load8<float>(s);
-}
-
-// Rows of Q [q0, q1) and of K and V [0, k1) that the units' items read (whole query and key tiles)
-static void cvt_rows(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, int *q0, int *q1, int *k1) {
-  int lo = qkv->n, hi = 0;
-  for (int i = 0; i < nunits; ++i) {
-    lo = std::min(lo, units[i].s0);
-    hi = std::max(hi, units[i].s1);
+  int lo = blockIdx.y, b = blockIdx.x;
+  if (gridDim.y == 1) {
+    int hi = a.nheads - 1;
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (a.head[mid].start <= b) lo = mid;
+      else hi = mid - 1;
+    }
+    b -= a.head[lo].start;
   }
-  *q0 = std::max(0, lo / 128 * 128);
-  *q1 = std::min(qkv->n, (hi + 127) / 128 * 128);
-  *k1 = qkv->n;  // the kernels bound their reads by the sequence
+  const CvtHead e = a.head[lo];
+  const CvtArray X = a.x[e.which & 3];
+  const int h = e.which >> 2, x = b * 256 + (int)threadIdx.x, r = x >> a.lgc, c = x & ((1 << a.lgc) - 1);
+  if (r >= e.rows) return;
+  const long long row = e.row0 + r;
+  *(u32x4 *)(X.dst + h * X.dh + row * a.d + 8 * c) = load8<float>(X.src + h * X.sh + row * X.st + 8 * c);
 }
 
-size_t attn_cvt_bytes(const rs_qkv *qkv, const rs_unit *units, int32_t nunits) {
-  if (!qkv || qkv->dtype != RS_F32 || nunits <= 0) return 0;
-  int q0, q1, k1;
-  cvt_rows(qkv, units, nunits, &q0, &q1, &k1);
-  if (q1 <= q0) return 0;
+// What a conversion for these units covers.
+struct CvtPlan {
+  int h0 = 0, h1 = 0, g0 = 0, g1 = 0;  // the copies hold query heads [h0, h1), key/value heads [g0, g1)
+  int q0 = 0, q1 = 0, k1 = 0;          // ... rows [q0, q1), keys [0, k1)
+  std::vector<int> qa, qb, kb;         // rows [qa, qb) of query head h, keys [0, kb) of key/value head g
+  long long read = 0;                  // elements converted, V apart
+  long long read_v = 0;
+};
+static CvtPlan cvt_plan(const rs_qkv *qkv, const rs_unit *units, int32_t nunits) {
+  CvtPlan p;
+  const int group = qkv->hq / qkv->hkv, n = qkv->n;
+  p.qa.assign(qkv->hq, n);
+  p.qb.assign(qkv->hq, 0);
+  p.kb.assign(qkv->hkv, 0);
+  p.h0 = qkv->hq;
+  p.g0 = qkv->hkv;
+  p.q0 = n;
+  for (int i = 0; i < nunits; ++i) {
+    const rs_unit &u = units[i];
+    if (u.head < 0 || u.head >= qkv->hq || u.s0 < 0 || u.s1 <= u.s0 || u.s1 > n) continue;  // a size query's
+    const int g = u.head / group;
+    // whole query tiles of 128 rows and key tiles of 64
+    p.qa[u.head] = std::min(p.qa[u.head], u.s0 / 128 * 128);
+    p.qb[u.head] = std::max(p.qb[u.head], std::min(n, (u.s1 + 127) / 128 * 128));
+    p.kb[g] = std::max(p.kb[g], std::min(n, (u.s1 + 63) / 64 * 64));
+    p.h0 = std::min(p.h0, u.head);
+    p.h1 = std::max(p.h1, u.head + 1);
+    p.g0 = std::min(p.g0, g);
+    p.g1 = std::max(p.g1, g + 1);
+  }
+  for (int h = p.h0; h < p.h1; ++h) {
+    p.q0 = std::min(p.q0, p.qa[h]);
+    p.q1 = std::max(p.q1, p.qb[h]);
+    p.read += (long long)std::max(0, p.qb[h] - p.qa[h]) * qkv->d;
+  }
+  for (int g = p.g0; g < p.g1; ++g) {
+    p.k1 = std::max(p.k1, p.kb[g]);
+    p.read += (long long)p.kb[g] * qkv->d;
+    p.read_v += (long long)p.kb[g] * qkv->d;
+  }
+  return p;
+}
+
+static size_t cvt_plan_bytes(const rs_qkv *qkv, const CvtPlan &p, bool v) {
+  if (p.h1 <= p.h0) return 0;
   Arena ar(nullptr, 0);
-  ar.take<bf16>((size_t)qkv->hq * (q1 - q0) * qkv->d);
-  ar.take<bf16>((size_t)qkv->hkv * k1 * qkv->d);
-  ar.take<bf16>((size_t)qkv->hkv * k1 * qkv->d);
+  ar.take<bf16>((size_t)(p.h1 - p.h0) * (p.q1 - p.q0) * qkv->d);
+  ar.take<bf16>((size_t)(p.g1 - p.g0) * p.k1 * qkv->d);
+  if (v) ar.take<bf16>((size_t)(p.g1 - p.g0) * p.k1 * qkv->d);
   return ar.off + 256;
 }
 
-rs_status attn_cvt_launch(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, void *p, rs_qkv *out,
-                          hipStream_t st) {
-  int q0, q1, k1;
-  cvt_rows(qkv, units, nunits, &q0, &q1, &k1);
-  Arena ar(p, ~size_t(0));
-  const int d = qkv->d;
-  CvtArgs a{};
-  a.dst[0] = ar.take<bf16>((size_t)qkv->hq * (q1 - q0) * d);
-  a.dst[1] = ar.take<bf16>((size_t)qkv->hkv * k1 * d);
-  a.dst[2] = ar.take<bf16>((size_t)qkv->hkv * k1 * d);
-  a.src[0] = (const float *)qkv->q; a.src[1] = (const float *)qkv->k; a.src[2] = (const float *)qkv->v;
-  a.sh[0] = qkv->sq_h; a.sh[1] = qkv->sk_h; a.sh[2] = qkv->sv_h;
-  a.st[0] = qkv->sq_t; a.st[1] = qkv->sk_t; a.st[2] = qkv->sv_t;
-  a.r0[0] = q0;
-  a.rows[0] = q1 - q0; a.rows[1] = a.rows[2] = k1;
-  a.heads[0] = qkv->hq; a.heads[1] = a.heads[2] = qkv->hkv;
-  a.n = qkv->n; a.d = d; a.lgc = d == 128 ? 4 : 3;
-  const long long thr = (long long)std::max(q1 - q0, k1) << a.lgc;
-  hipLaunchKernelGGL(attn_cvt_kernel, dim3((unsigned)((thr + 255) / 256), qkv->hq + 2 * qkv->hkv), dim3(256), 0, st, a);
-  RS_HIP(hipGetLastError());
+// Time in us that bf16 tiles save a call of these units, on average over the candidates (ncand = 0: the
+// most that any candidate can save): tile steps of the launch (of its longest item, or of all items over
+// the 512 workgroups the chip holds) times what a step saves.  Measured per step, fp32 tiles against
+// bf16 tiles in memory, d = 128: dense 0.95 us in one chain of 512 tiles and 0.67 us with the chip full
+// (0.4 us with V^T); A-shape and block-sparse 1.0 to 1.2 us with the chip full; vertical-slash 2.2 to
+// 3.8 us.  A vertical-slash list is known on the device only: one tile per diagonal is assumed (apart
+// from each other they touch three, side by side a 64th).  With the conversion decided by this rule,
+// in place of converting every head's every row: one head's first 2048 tokens of 131072, 32/8 heads, 381 ->
+// 55 us (65 us with fp32 tiles); A-shape, 2048 rows x 32 heads at 64K, 221 -> 76 us; dense, 32/8 heads at
+// 8K, 542 -> 557 us (722 us with fp32 tiles).
+static double cvt_saves(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, const rs_candidate *grid,
+                        int32_t ncand) {
+  double sum = 0.0;
+  for (int c = 0; c < std::max(ncand, 1); ++c) {
+    double all = 0.0, longest = 0.0;
+    for (int i = 0; i < nunits; ++i) {
+      const rs_unit &u = units[i];
+      if (u.head < 0 || u.head >= qkv->hq || u.s0 < 0 || u.s1 <= u.s0 || u.s1 > qkv->n) continue;
+      const double full = (u.s1 + 63) / 64, mean = (u.s0 / 64 + full + 1) / 2;  // key tiles before the last row; on average
+      double most = full, us = 2.2;
+      if (ncand > 0) {
+        const rs_candidate &g = grid[c];
+        us = g.fam == RS_DENSE ? (qkv->vt ? 0.4 : 0.65) : g.fam == RS_VSLASH ? 2.2 : 1.0;
+        if (g.fam == RS_ASHAPE) most = std::min(full, (g.a + 63) / 64 + (g.b + 63) / 64 + 2.0);
+        if (g.fam == RS_VSLASH) most = std::min(full, g.a / 64 + g.b + 2.0);
+        if (g.fam == RS_BSPARSE) most = std::min(full, 1.5 * g.a);
+      }
+      const SplitRule sp = attn_split(qkv->hq, qkv->d, qkv->n, u.s0, u.s1, ncand > 0 ? grid[c].fam : RS_BSPARSE);
+      all += us * std::min(mean, most) * ((u.s1 - 1) / 128 - u.s0 / 128 + 1);
+      longest = std::max(longest, us * most / std::max(1, std::min(sp.nsplit, (int)most / sp.ptiles)));
+    }
+    sum += std::max(all / 512, longest);
+  }
+  return sum / std::max(ncand, 1);
+}
+
+// ... and what the conversion takes: its launch, and 6 bytes an element at the rate above.
+static double cvt_costs(const CvtPlan &p, bool v) { return 5.0 + (p.read + (v ? p.read_v : 0)) * 6.0 / 6.5e6; }
+
+size_t attn_cvt_bytes(const rs_qkv *qkv, const rs_unit *units, int32_t nunits) {
+  if (!qkv || qkv->dtype != RS_F32 || nunits <= 0 || qkv->hkv < 1 || qkv->hq < qkv->hkv || qkv->n < 1) return 0;
+  const CvtPlan p = cvt_plan(qkv, units, nunits);
+  return cvt_saves(qkv, units, nunits, nullptr, 0) > cvt_costs(p, !qkv->vt) ? cvt_plan_bytes(qkv, p, true) : 0;
+}
+
+rs_status attn_cvt_launch(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, const rs_candidate *grid,
+                          int32_t ncand, void *ws, size_t room, rs_qkv *out, hipStream_t st) {
   *out = *qkv;
+  if (qkv->dtype != RS_F32 || !ws || ((uintptr_t)ws & 15)) return RS_OK;
+  bool v = !qkv->vt;  // vertical-slash items gather rows of V itself
+  for (int c = 0; c < ncand; ++c) v = v || grid[c].fam == RS_VSLASH;
+  const CvtPlan p = cvt_plan(qkv, units, nunits);
+  if (cvt_plan_bytes(qkv, p, v) > room || cvt_saves(qkv, units, nunits, grid, ncand) <= cvt_costs(p, v)) return RS_OK;
+  const int d = qkv->d;
+  const long long rows = p.q1 - p.q0;
+  Arena ar(ws, room);
+  bf16 *q = ar.take<bf16>((size_t)(p.h1 - p.h0) * rows * d);
+  bf16 *k = ar.take<bf16>((size_t)(p.g1 - p.g0) * p.k1 * d);
+  bf16 *vv = v ? ar.take<bf16>((size_t)(p.g1 - p.g0) * p.k1 * d) : k;  // else V is not read
+  const long long dq = rows * d, dk = (long long)p.k1 * d;
+  CvtArgs a;
+  a.x[0] = CvtArray{(const float *)qkv->q, q - p.h0 * dq - (long long)p.q0 * d, qkv->sq_h, qkv->sq_t, dq};
+  a.x[1] = CvtArray{(const float *)qkv->k, k - p.g0 * dk, qkv->sk_h, qkv->sk_t, dk};
+  a.x[2] = CvtArray{(const float *)qkv->v, vv - p.g0 * dk, qkv->sv_h, qkv->sv_t, dk};
+  a.d = d;
+  a.lgc = d == 128 ? 4 : 3;
+  a.nheads = a.blocks = 0;
+  const int rpw = 256 >> a.lgc;  // rows of a workgroup
+  int per = 0;                   // workgroups of the longest head
+  auto flush = [&]() -> rs_status {
+    if (a.nheads == 0) return RS_OK;
+    const bool even = (long long)per * a.nheads * 4 <= (long long)a.blocks * 5;
+    hipLaunchKernelGGL(attn_cvt_kernel, even ? dim3(per, a.nheads) : dim3(a.blocks), dim3(256), 0, st, a);
+    RS_HIP(hipGetLastError());
+    a.nheads = a.blocks = per = 0;
+    return RS_OK;
+  };
+  auto add = [&](int head, int which, int row0, int n) -> rs_status {
+    if (n <= 0) return RS_OK;
+    a.head[a.nheads++] = CvtHead{4 * head + which, row0, n, a.blocks};
+    a.blocks += (n + rpw - 1) / rpw;
+    per = std::max(per, (n + rpw - 1) / rpw);
+    return a.nheads == kCvtHeads ? flush() : RS_OK;
+  };
+  rs_status s = RS_OK;
+  for (int h = p.h0; h < p.h1 && s == RS_OK; ++h) s = add(h, 0, p.qa[h], p.qb[h] - p.qa[h]);
+  for (int w = 1; w <= (v ? 2 : 1); ++w)
+    for (int g = p.g0; g < p.g1 && s == RS_OK; ++g) s = add(g, w, 0, p.kb[g]);
+  if (s == RS_OK) s = flush();
+  if (s != RS_OK) return s;
   out->dtype = RS_BF16;
-  out->q = a.dst[0] - (long long)q0 * d;  // rows before q0 are not read
-  out->k = a.dst[1];
-  out->v = a.dst[2];
-  out->sq_h = (int64_t)(q1 - q0) * d;
-  out->sk_h = out->sv_h = (int64_t)k1 * d;
+  out->q = a.x[0].dst;
+  out->k = a.x[1].dst;
+  out->v = a.x[2].dst;
+  out->sq_h = dq;
+  out->sk_h = out->sv_h = dk;
   out->sq_t = out->sk_t = out->sv_t = d;
   return RS_OK;
 }
@@ -1537,13 +1655,12 @@ rs_status attn_launch(const rs_qkv *qkv, float scale, const rs_unit *units, int3
   char *at = (char *)ws + lbytes / 256 * 256;  // past the list's end
   if (slots > 0) parts = attn_parts_at(at, qkv->d, slots);
   at += attn_parts_bytes(qkv->d, slots) / 256 * 256;
-  const size_t cvt = attn_cvt_bytes(qkv, units, nunits);
+  const size_t used = (size_t)(at - (char *)ws);
+  const rs_candidate own = cand ? *cand : rs_candidate{RS_DENSE, 0, 0, 0};
   rs_qkv conv;
-  if (cvt > 0 && !((uintptr_t)ws & 15) && ws_bytes >= (size_t)(at - (char *)ws) + cvt) {
-    rs_status rc = attn_cvt_launch(qkv, units, nunits, at, &conv, st);
-    if (rc != RS_OK) return rc;
-    qkv = &conv;
-  }
+  rs_status rc = attn_cvt_launch(qkv, units, nunits, &own, 1, at, ws_bytes > used ? ws_bytes - used : 0, &conv, st);
+  if (rc != RS_OK) return rc;
+  qkv = &conv;
   std::vector<DevUnit> du(nunits);
   int pbase = 0;
   for (int u = 0; u < nunits; ++u) {

@@ -115,11 +115,13 @@ rs_status attn_merge_launch(const rs_qkv *qkv, float scale, const DevUnit *d_uni
                             int nitems, void *o, int64_t so_h, int64_t so_t, float *lse, hipStream_t st);
 
 // fp32 Q, K and V rounded to bf16 in the workspace before the attention, as the kernels would on
-// load: rows the units read, [head][token][d].  bytes: 0 for bf16 inputs.
+// load: the heads and rows that the units read.  bytes: room for it; 0 for bf16 inputs and for
+// calls that read their inputs too rarely, whatever their family, to gain from it.
 size_t attn_cvt_bytes(const rs_qkv *qkv, const rs_unit *units, int32_t nunits);
-// Queues the conversion into `p` and describes the result in *out (qkv with bf16 arrays).
-rs_status attn_cvt_launch(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, void *p, rs_qkv *out,
-                          hipStream_t st);
+// Queues the conversion into `ws` where the workspace has room for it and calls over these candidates
+// gain from it.  *out: the layer to run on (bf16 copies, or *qkv itself).
+rs_status attn_cvt_launch(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, const rs_candidate *grid,
+                          int32_t ncand, void *ws, size_t room, rs_qkv *out, hipStream_t st);
 
 // Device work queues of the persistent attention launches: per family f and key/value bucket b
 // (q = 8 f + b), the items order[off[q] .. off[q] + size[q]) and a counter of items taken (starts

@@ -809,14 +809,12 @@ rs_status routed_attn_launch(const rs_qkv *qkv, float scale, const rs_unit *unit
   char *at = (char *)ws + need / 256 * 256;  // past the lists' end
   if (slots > 0) parts = attn_parts_at(at, qkv->d, slots);
   at += attn_parts_bytes(qkv->d, slots) / 256 * 256;
-  const size_t cvt = attn_cvt_bytes(qkv, units, nunits);
+  const size_t used = (size_t)(at - (char *)ws);
   const rs_unit_table *tables = qkv->tables;
   rs_qkv conv;
-  if (cvt > 0 && !((uintptr_t)ws & 15) && ws_bytes >= (size_t)(at - (char *)ws) + cvt) {
-    rs_status s = attn_cvt_launch(qkv, units, nunits, at, &conv, st);
-    if (s != RS_OK) return s;
-    qkv = &conv;
-  }
+  rs_status sc = attn_cvt_launch(qkv, units, nunits, grid, ncand, at, ws_bytes > used ? ws_bytes - used : 0, &conv, st);
+  if (sc != RS_OK) return sc;
+  qkv = &conv;
   Arena ar(ws, ws_bytes);
   rs_unit *d_units = ar.take<rs_unit>((size_t)nunits);
   int *d_q = ar.take<int>(3 * 32);

@@ -44,3 +44,26 @@ def test_partial_results_are_bounded(n, seg, hq, hkv, d):
 def test_a_chunk_at_the_end_has_room_for_its_pieces():
     whole, _, units, tiles = _sizes(65536, 512, 32, 8, first=65536 - 512)
     assert whole > tiles * 2 * 128 * 130 * 4  # at least two pieces an item
+
+
+def test_fp32_copies_cover_the_units_only():
+    """One head's first 2048 tokens of a long fp32 context: its rows, not the layer's; and none for a
+    call that reads too little to gain from copies."""
+    n, hq, hkv, d = 131072, 32, 8, 128
+    qkv = _rs.RsQkv(q=16, k=16, v=16, dtype=1, n=n, hq=hq, hkv=hkv, d=d, sq_h=n * d, sq_t=d, sk_h=n * d, sk_t=d,
+                    sv_h=n * d, sv_t=d)
+    L = _rs.lib()
+
+    def size(units):
+        u = _rs.make_units(units)
+        return (L.rs_attn_workspace_size(C.byref(qkv), u, len(units)),
+                L.rs_routed_attn_workspace_size(C.byref(qkv), u, len(units)))
+
+    rows = 3 * 2048 * d * 2
+    for got in size([(3, 0, 2048)]):
+        assert rows <= got <= rows + 16384
+    for got in size([(3, 0, 64)]):
+        assert got <= 4096
+    whole = (hq + 2 * hkv) * n * d * 2
+    for got in size([(h, 0, n) for h in range(hq)]):
+        assert whole <= got <= whole + MIB
