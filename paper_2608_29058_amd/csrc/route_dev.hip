@@ -226,7 +226,9 @@ __global__ void __launch_bounds__(1024) route_kernel(const RouteArgs a) {
       const int c = sPath[u * W + j];
       const double rho = (sR[c * U + u] - sR[cur * U + u]) / (sT[cur * U + u] - sT[c * U + u]);
       K = (j == 0 || rho > K) ? rho : K;
-      sKey[base + j] = K;
+      // undefined ratios (NaN coverage) go last: with NaN keys the sort's outcome would depend on the
+      // order in which the waves took their places in the list
+      sKey[base + j] = K == K ? K : (double)INFINITY;
       sId[base + j] = u * W + j;
       cur = c;
     }
