@@ -82,13 +82,19 @@ constexpr int kDirectUnits = 64;
 // Workgroup b runs on XCD b % 8 (round-robin dispatch), so a fixed bucket per XCD gives the query heads
 // of one key/value head one L2, but also ties an XCD's work to its bucket's.  Vertical-slash heads
 // keep very different numbers of tiles (and block-sparse mates unite to different numbers), so the
-// XCD with the heaviest bucket ran alone at the end.  The buckets therefore move on by one XCD every
-// kRotate items of a bucket: long enough stays for the items that share tiles, short enough for an
-// even mix.  Measured with 8 key/value heads, fixed buckets -> rotation: vertical-slash n = 32768
-// (1000, 512) 5.24 -> 2.65 ms, (1000, 6096) 8.55 -> 7.72 ms, n = 16384 1.59 -> 1.15 ms, n = 4096 192
-// -> 176 us (every item: 3.62, 8.50, 1.33 ms and 186 us; every 64 items: 2.77, 7.82, 1.21 ms and
-// 185 us); block-sparse n = 131072 18.3 -> 15.2 ms, n = 32768 3.70 -> 3.20 ms, n = 4096 119 -> 117 us
-// (every 16 items: 15.4, 3.25 ms and 115 us).  Dense and A-shape heads weigh the same.
+// XCD with the heaviest bucket ran alone at the end.  The buckets therefore move on by one XCD after a
+// stay of kRotate items per XCD that a bucket has (with na buckets left each has 8 / na): long
+// enough for the items that share tiles, short enough for an even mix.  What it gives depends on how
+// uneven the heads are.  Attention calls with fixed buckets -> rotation:
+//   one key/value head diffuse (vertical, sink or local the others), 32/8 heads: vertical-slash (1000, 512)
+//   n = 16384 2.09 -> 1.31 ms, (1000, 6096) n = 32768 8.75 -> 7.13 ms, block-sparse n = 131072 (100 blocks)
+//   21.0 -> 15.5 ms; 28/4 heads: 1.75 -> 1.38, 7.29 -> 6.47, 17.9 -> 15.2 ms;
+//   even heads, 32/8: 1.07 -> 1.00, 6.73 -> 6.50, 14.2 -> 14.1 ms; 28/4: 0.86 -> 0.86, 5.55 -> 5.47, 13.0 ->
+//   13.1 ms; 8/2 heads: 0.30 -> 0.29, 1.52 -> 1.56, 3.44 -> 3.47 ms (within 2% either way over inputs).
+// Stays of kRotate items whatever the number of buckets were 2 to 7% slower than fixed buckets for even
+// heads at 2 and 4 key/value heads.  At 8, other stays: vertical-slash n = 32768 every item 3.62, 16 items
+// 2.65, 64 items 2.77 ms; block-sparse n = 32768 16 items 3.25, 64 items 3.20 ms.  Dense and A-shape
+// heads weigh the same.
 template <int PAT>
 constexpr int kRotate = PAT == P_VS ? 16 : PAT == P_BS ? 64 : 0;
 
@@ -960,7 +966,7 @@ __global__ void __launch_bounds__(256, 2) attn_fwd_kernel(const AttnDirect p) {
     while (k + 1 < p.nseg && x >= p.pos[k + 1]) ++k;
     const int rem = x - p.pos[k], turn = rem / p.na[k];
     int j = rem - turn * p.na[k];
-    if constexpr (kRotate<PAT> > 0) j = (j + turn / kRotate<PAT>) % p.na[k];
+    if constexpr (kRotate<PAT> > 0) j = (j + turn / (kRotate<PAT> * 8 / p.na[k])) % p.na[k];
     const int b = __builtin_amdgcn_readfirstlane((int)(p.act[k] >> (4 * j)) & 7);
     const int i = p.first[k] + turn;  // item i of bucket b
     // longest query tiles first, then the bucket's units, then the pieces of an item
@@ -1452,7 +1458,8 @@ static void pair_units(const rs_unit *units, int nunits, int group, std::vector<
 // dispatch places workgroup b on XCD b % 8, so the query heads sharing one K/V stream
 // share one XCD's L2), longest query tiles first within a bucket.  Items of a unit with a
 // mate are 64-row query blocks, others bm-row query tiles (bm = 128); units taken along by a
-// mate have none.  Pieces of a split item follow one another.  rotate: as kRotate.
+// mate have none.  Pieces of a split item follow one another.  rotate: kRotate of the pattern, applied
+// as attn_fwd_kernel does.
 static void build_order(const rs_unit *units, int nunits, int group, int bm, int rotate, const std::vector<int> &mate,
                         const std::vector<SplitRule> &split, std::vector<int> &order) {
   std::vector<std::vector<std::pair<int, int>>> buckets(8);  // (-first row / 64, item)
@@ -1472,11 +1479,17 @@ static void build_order(const rs_unit *units, int nunits, int group, int bm, int
     mx = std::max(mx, b.size());
   }
   order.clear();
+  size_t first = 0;  // item from which the buckets now left take turns
+  int left = 0;
   for (size_t i = 0; i < mx; ++i) {
     int act[8], na = 0;
     for (int b = 0; b < 8; ++b)
       if (i < buckets[b].size()) act[na++] = b;
-    for (int j = 0; j < na; ++j) order.push_back(buckets[act[(j + (rotate ? i / rotate : 0)) % na]][i].second);
+    if (na != left) {
+      left = na;
+      first = i;
+    }
+    for (int j = 0; j < na; ++j) order.push_back(buckets[act[(j + (rotate ? (i - first) / (rotate * 8 / na) : 0)) % na]][i].second);
   }
 }
 
