@@ -75,7 +75,8 @@ struct DevUnit {
 //     of a local one), so they are split into up to three rounds of workgroups (at most 768 items):
 //     2048 rows x 32 heads at 50K keys took 1759 us in one piece and 1275 us in up to four with the mask
 //     words fetched once per wave, which alone gives 1.17x; the whole call (probe, indices, attention)
-//     of the same shape on other inputs takes 587 us with four pieces and 566 us with three.
+//     of the same shape takes 587 us with four pieces and 566 us with three on one set of inputs,
+//     694 and 708 us on another.
 //   * A piece writes and the merge reads d + 2 floats per row: pieces are long enough (32 and 64
 //     tiles) to make that small, or 8 tiles where all partial results together stay in cache.
 // A-shape lists are short and block-sparse ones are even: neither is split.

@@ -25,8 +25,8 @@
 namespace rs {
 
 constexpr int kProbeMaxRows = 256;  // sampled rows per unit
-// keys per workgroup range in the three passes: a power of two in [kMinRange, kMaxRange]
-// (probe_range), in an order that halves a launch's serial tiles where it would not fill the chip
+// keys per workgroup range in the three passes: a power of two in [kMinRange, kMaxRange], the
+// longest, halved while a launch would not fill the chip (probe_range)
 constexpr int kMinRange = 128, kMaxRange = 1024;
 constexpr int kMaxCand = 16;
 constexpr int kPrefVs = 3;   // vertical-slash candidates whose bitmap words are prefetched
@@ -369,10 +369,11 @@ __global__ void __launch_bounds__(256, 2) probe_range_kernel(const ProbeArgs a) 
     }
 
     // coverage pass, per range: the block-sparse selection word of each row's query block (the
-    // range's 16 key blocks share one word), the range's 32 column-bitmap words (lane w holds
-    // word c0 / 32 + w) and, when they fit in sDW, the diagonal-bitmap words of every window
-    // the rows read here: window positions i - k0 - 63 lie in [r_lo - c0 - 1023, r_hi - c0 - 63]
-    // for the pair's rows [r_lo, r_hi], and a window reads its word and the next two
+    // range's key blocks, at most 16 and aligned to their number, share one word), the range's
+    // column-bitmap words, at most 32 (lane w holds word c0 / 32 + w) and, when they fit in sDW,
+    // the diagonal-bitmap words of every window the rows read here: window positions i - k0 - 63
+    // lie in [r_lo - c0 - (range - 1), r_hi - c0 - 63] for the pair's rows [r_lo, r_hi], and a
+    // window reads its word and the next two
     uint32_t bwr[2][kPrefBs], vmv[kPrefVs];
     int rlo = 0, dw0 = 0;
     bool stage = false;
@@ -880,9 +881,10 @@ __global__ void probe_finish_kernel(const ProbeArgs a, float *diag, float *entro
 // w = exp(m - M); Z = sum w z, m_i(c) = sum w cov(c) / Z, local mass likewise, and with
 // S = sum over 64-key blocks of B log B (B relative to M) = sum w (s + log(w) z), the block
 // entropy is log Z - S / Z.  Writes row_max / row_sum, the descriptors and m_i(c).
-// grid (ceil(rmax / 4), nunits), 256 threads
-// sixteen lanes per row (a row has at most n / 1024 ranges): four rows per wave, more loads
-// in flight per lane than one row per wave; the sixteen lanes reduce with a fixed butterfly
+// grid (ceil(rmax / 16), nunits), 256 threads
+// sixteen lanes per row (a row has n / range ranges, 128 where a 128K prompt's launch takes the longest):
+// four rows per wave, more loads in flight per lane than one row per wave; the sixteen lanes
+// reduce with a fixed butterfly
 __global__ void cover_combine_kernel(const ProbeArgs a, float *entropy, float *local, float *cov_rows) {
   const int u = blockIdx.y;
   const ProbeUnit U = a.units[u];
