@@ -349,9 +349,10 @@ rs_status rs_transpose_v(const rs_qkv *qkv, void *vt, rs_stream stream);
  * disjoint rows.
  * The workspace holds the work lists, the partial results of items split along their keys and
  * bf16 copies of fp32 inputs.  Only dense and vertical-slash items of units that end with the
- * sequence (s1 = n) are split, so the partial results stay below 1536 x 128 x (d + 2) floats
- * (98 MiB at d = 128) for any list that covers the last rows of each head once; the lists take
- * some tens of bytes per unit and 128 rows.  The copies hold the heads and rows that the units
+ * sequence (s1 = n; a chunk in front of the unused rest of a longer K/V buffer is described with
+ * n = s1) are split, so the partial results stay below 1536 x 128 x (d + 2) floats (98 MiB at
+ * d = 128) for any list that covers the last rows of each head once; the lists take some tens of
+ * bytes per unit and 128 rows.  The copies hold the heads and rows that the units
  * read, for calls that read them often enough to gain from it.  The size query counts all three;
  * with a workspace that has room for the lists but not for the rest, items run unsplit (their
  * rows then differ in the last bits, as the partial sums add in another order) and fp32 inputs

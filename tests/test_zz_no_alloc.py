@@ -1,8 +1,7 @@
-"""rs_route_layer_device_noalloc (the router's scratch in a fixed library-owned device array)
-against rs_route_layer_device (caller workspace) on the same inputs: identical routes, risks,
-lower masses, groups, status and totals, bit for bit, on two calls in a row, the second with
-fewer units and candidates than the first (the scratch keeps the first call's contents).
-Sizes beyond the fixed array are rejected on the host, before any launch."""
+"""rs_route_layer_device_noalloc (no workspace argument) against rs_route_layer_device on the same
+inputs: identical routes, risks, lower masses, groups, status and totals, bit for bit, on two calls
+in a row, the second with fewer units and candidates than the first (nothing of the first is left).
+Sizes beyond the router's LDS are rejected on the host, before any launch."""
 import ctypes as C
 
 import numpy as np
