@@ -1144,44 +1144,49 @@ static size_t cvt_plan_bytes(const rs_qkv *qkv, const CvtPlan &p, bool v) {
   return ar.off + 256;
 }
 
-// Time in us that bf16 tiles save a call of these units, on average over the candidates (ncand = 0: the
-// most that any candidate can save): tile steps of the launch (of its longest item, or of all items over
-// the 512 workgroups the chip holds) times what a step saves.  Measured per step, fp32 tiles against
-// bf16 tiles in memory, d = 128: dense 0.95 us in one chain of 512 tiles and 0.67 us with the chip full
-// (0.4 us with V^T); A-shape and block-sparse 1.0 to 1.2 us with the chip full; vertical-slash 2.2 to
-// 3.8 us.  A vertical-slash list is known on the device only: one tile per diagonal is assumed (apart
-// from each other they touch three, side by side a 64th).  With the conversion decided by this rule,
-// in place of converting every head's every row: one head's first 2048 tokens of 131072, 32/8 heads, 381 ->
-// 55 us (65 us with fp32 tiles); A-shape, 2048 rows x 32 heads at 64K, 221 -> 76 us; dense, 32/8 heads at
-// 8K, 542 -> 557 us (722 us with fp32 tiles).
+// Time in us that bf16 copies save a call of these units, on average over the candidates (ncand = 0: the
+// most that any candidate can save): what a tile step saves in a chain of them, times the steps of the
+// launch's longest item, and with the chip full, times all steps over the 512 workgroups that it holds.
+// Both, and the costs below, were fitted to the times of 740 calls with and without the conversion (every
+// family, 1 to 64 heads, 300 to 8192 tokens, whole prompts and chunks): over them the rule is 0.2% slower
+// than the better choice each time, converting always 3.4% and never 24%.  fp32 tiles at d = 128 cost
+// most where their lists are gathered or uneven (vertical-slash).  A vertical-slash list is known on
+// the device only: one tile per diagonal is assumed (apart from each other diagonals touch three, side by
+// side a 64th).  Examples: one head's first 2048 tokens of 131072, 32/8 heads: 65 us with fp32 tiles, 55 us
+// with copies of what it reads (381 us with copies of everything); A-shape, 2048 rows x 32 heads at 64K:
+// 76 us with fp32 tiles (chosen), 221 us with copies; dense, 32/8 heads at 8K: 722 and 557 us.
+constexpr double kCvtFull[4][2] = {{0.16, 0.37}, {0.26, 0.72}, {0.63, 1.74}, {0.19, 1.10}};   // [family][d = 128]
+constexpr double kCvtChain[4][2] = {{0.45, 0.59}, {0.38, 0.59}, {0.45, 1.50}, {0.26, 1.13}};
 static double cvt_saves(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, const rs_candidate *grid,
                         int32_t ncand) {
   double sum = 0.0;
   for (int c = 0; c < std::max(ncand, 1); ++c) {
-    double all = 0.0, longest = 0.0;
+    const int fam = ncand > 0 ? grid[c].fam : RS_VSLASH, a = ncand > 0 ? grid[c].a : 0, b = ncand > 0 ? grid[c].b : 0;
+    double all = 0.0, longest = 0.0;  // tile steps
     for (int i = 0; i < nunits; ++i) {
       const rs_unit &u = units[i];
       if (u.head < 0 || u.head >= qkv->hq || u.s0 < 0 || u.s1 <= u.s0 || u.s1 > qkv->n) continue;
       const double full = (u.s1 + 63) / 64, mean = (u.s0 / 64 + full + 1) / 2;  // key tiles before the last row; on average
-      double most = full, us = 2.2;
+      double most = full;
+      SplitRule sp{1, 1};
       if (ncand > 0) {
-        const rs_candidate &g = grid[c];
-        us = g.fam == RS_DENSE ? (qkv->vt ? 0.4 : 0.65) : g.fam == RS_VSLASH ? 2.2 : 1.0;
-        if (g.fam == RS_ASHAPE) most = std::min(full, (g.a + 63) / 64 + (g.b + 63) / 64 + 2.0);
-        if (g.fam == RS_VSLASH) most = std::min(full, g.a / 64 + g.b + 2.0);
-        if (g.fam == RS_BSPARSE) most = std::min(full, 1.5 * g.a);
+        if (fam == RS_ASHAPE) most = std::min(full, (a + 63) / 64 + (b + 63) / 64 + 2.0);
+        if (fam == RS_VSLASH) most = std::min(full, a / 64 + b + 2.0);
+        if (fam == RS_BSPARSE) most = std::min(full, 1.5 * a);  // of two query blocks
+        sp = attn_split(qkv->hq, qkv->d, qkv->n, u.s0, u.s1, fam);
       }
-      const SplitRule sp = attn_split(qkv->hq, qkv->d, qkv->n, u.s0, u.s1, ncand > 0 ? grid[c].fam : RS_BSPARSE);
-      all += us * std::min(mean, most) * ((u.s1 - 1) / 128 - u.s0 / 128 + 1);
-      longest = std::max(longest, us * most / std::max(1, std::min(sp.nsplit, (int)most / sp.ptiles)));
+      all += std::min(mean, most) * ((u.s1 - 1) / 128 - u.s0 / 128 + 1);
+      longest = std::max(longest, most / std::max(1, std::min(sp.nsplit, (int)most / sp.ptiles)));
     }
-    sum += std::max(all / 512, longest);
+    const double us = kCvtFull[fam][qkv->d == 128] * all / 512 + kCvtChain[fam][qkv->d == 128] * longest;
+    // with V^T only K goes through registers (dense, 32/8 heads at 8K: 100 us saved instead of 170)
+    sum += ncand > 0 && qkv->vt && fam != RS_VSLASH ? 0.6 * us : us;
   }
   return sum / std::max(ncand, 1);
 }
 
-// ... and what the conversion takes: its launch, and 6 bytes an element at the rate above.
-static double cvt_costs(const CvtPlan &p, bool v) { return 5.0 + (p.read + (v ? p.read_v : 0)) * 6.0 / 6.5e6; }
+// ... and what the conversion takes: its launch, and 6 bytes an element at 8.1 TB/s.
+static double cvt_costs(const CvtPlan &p, bool v) { return 3.4 + (p.read + (v ? p.read_v : 0)) * 6.0 / 8.1e6; }
 
 size_t attn_cvt_bytes(const rs_qkv *qkv, const rs_unit *units, int32_t nunits) {
   if (!qkv || qkv->dtype != RS_F32 || nunits <= 0 || qkv->hkv < 1 || qkv->hq < qkv->hkv || qkv->n < 1) return 0;
