@@ -185,9 +185,16 @@ extern "C" {
 const char *rs_last_error(void) { return g_err.c_str(); }
 const char *rs_version(void) { return "routesparse-mi355x 0.1 (gfx950)"; }
 
+// The layer as the size queries of the attention read it: NULL (work lists only) for one whose calls
+// are refused, whose head counts and sizes would not fit the units.
+static const rs_qkv *sized_layer(const rs_qkv *qkv) {
+  const bool ok = qkv && qkv->n >= 1 && qkv->n <= kMaxN && qkv->hq >= 1 && qkv->hkv >= 1 && qkv->hq % qkv->hkv == 0;
+  return ok ? qkv : nullptr;
+}
+
 size_t rs_attn_workspace_size(const rs_qkv *qkv, const rs_unit *units, int32_t nunits) {
   if (nunits <= 0 || !units) return 256;
-  return attn_ws_bytes(qkv, units, nunits);
+  return attn_ws_bytes(sized_layer(qkv), units, nunits);
 }
 
 rs_status rs_dense_attn_prefill(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, void *o, int64_t so_h,
@@ -449,7 +456,7 @@ rs_status rs_error_predict(const rs_probe_out *probe, const rs_candidate *grid, 
 
 size_t rs_routed_attn_workspace_size(const rs_qkv *qkv, const rs_unit *units, int32_t nunits) {
   if (nunits <= 0 || !units) return 256;
-  return routed_attn_ws_bytes(qkv, units, nunits);
+  return routed_attn_ws_bytes(sized_layer(qkv), units, nunits);
 }
 
 rs_status rs_routed_attn_prefill(const rs_qkv *qkv, const rs_unit *units, int32_t nunits, const rs_candidate *grid,

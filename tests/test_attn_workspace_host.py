@@ -67,3 +67,14 @@ def test_fp32_copies_cover_the_units_only():
     whole = (hq + 2 * hkv) * n * d * 2
     for got in size([(h, 0, n) for h in range(hq)]):
         assert whole <= got <= whole + MIB
+
+
+@pytest.mark.parametrize("hq,hkv,n,d", [(1999, 1000, 4096, 128), (5, 2, 4096, 128), (2, 5, 4096, 64), (7, 7, 0, 128), (3, 0, 100, 64)])
+def test_size_queries_of_refused_layers_return(hq, hkv, n, d):
+    """Layers and units that the calls refuse: the queries read nothing outside their lists."""
+    qkv = _rs.RsQkv(q=16, k=16, v=16, dtype=1, n=n, hq=hq, hkv=hkv, d=d)
+    L = _rs.lib()
+    for units in ([(h, 0, 4096) for h in range(hq)], [(-1, 0, 10)], [(99, 5, 10)], [(0, 90, 10)], [(0, -5, 10)]):
+        u = _rs.make_units(units)
+        assert L.rs_attn_workspace_size(C.byref(qkv), u, len(units)) > 0
+        assert L.rs_routed_attn_workspace_size(C.byref(qkv), u, len(units)) > 0
